@@ -79,8 +79,8 @@ size_t workspace_bytes_for(int64_t B, int64_t N, int64_t H, int64_t D, int32_t w
   if (check_sizes(B, N, H, D, w1, w2, dtype) != SA_OK) return 0;
   if (choose_path(1, B, N, H, D, w1, w2, dtype) == Path::Mfma)
     return sa::mfma_bwd_plan(make_shape(B, N, H, D, w1, w2, 1.0f, dtype)).bytes;
-  // Delta: one float per (b, h, query), rounded up to 256 bytes.
-  return ((static_cast<size_t>(B * H * N) * sizeof(float)) + 255) & ~size_t(255);
+  const Shape s = make_shape(B, N, H, D, w1, w2, 1.0f, dtype);
+  return sa::f32_bwd_plan(s).bytes;
 }
 
 // Backward workspace of the determinant logits: the MFMA plan (with the dQ~
@@ -153,7 +153,7 @@ int forward(const void* q, const void* k, const void* kp, const void* v, const v
   s.vp_bias = vp_bias;
   hipStream_t st = static_cast<hipStream_t>(stream);
   switch (choose_path(0, B, N, H, D, w1, w2, dtype)) {
-    case Path::Generic: return to_status(sa::generic_fwd(s, q, k, kp, v, vp, out, lse, st));
+    case Path::Generic: return to_status(sa::f32_fwd(s, q, k, kp, v, vp, out, lse, st));
     case Path::Mfma: return to_status(sa::mfma_fwd(s, q, k, kp, v, vp, out, lse, st));
     default: return SA_ERR_UNSUPPORTED;
   }
@@ -171,8 +171,14 @@ int run_stage(const Shape& s, Path path, BwdStage stage, const void* q, const vo
   if (path == Path::Mfma)
     return to_status(
         sa::mfma_bwd_stage(s, stage, q, k, kp, v, vp, dout, lse, g0, g1, g2, workspace, st));
-  return to_status(sa::generic_bwd_stage(s, stage, q, k, kp, v, vp, dout, lse,
-                                         static_cast<const float*>(workspace), g0, g1, g2, st));
+  // Trilinear logits take the float32 MFMA kernels; determinant logits and the
+  // query side of w2 > 128 (whose k-rows overflow the LDS ring) the plain ones.
+  const float* delta = static_cast<const float*>(workspace);
+  if (s.form == 0 && (stage == BwdStage::Key || sa::f32_bwd_query_supported(s))) {
+    float* halo = reinterpret_cast<float*>(static_cast<char*>(workspace) + sa::f32_bwd_plan(s).halo_off);
+    return to_status(sa::f32_bwd_stage(s, stage, q, k, kp, v, vp, dout, lse, delta, g0, g1, g2, halo, st));
+  }
+  return to_status(sa::generic_bwd_stage(s, stage, q, k, kp, v, vp, dout, lse, delta, g0, g1, g2, st));
 }
 
 // ---- device scratch of the allocation-free backward ----
@@ -395,8 +401,7 @@ int simplicial_attn_bwd_noalloc(const void* q, const void* k, const void* kp, co
   Shape s = make_shape(B, N, H, D, w1, w2, scale, dtype);
   s.ws_cap = kScratchBytes;
   const Path path = choose_path(1, B, N, H, D, w1, w2, dtype);
-  const size_t need = path == Path::Mfma ? sa::mfma_bwd_plan(s).bytes
-                                         : workspace_bytes_for(B, N, H, D, w1, w2, dtype);
+  const size_t need = path == Path::Mfma ? sa::mfma_bwd_plan(s).bytes : sa::f32_bwd_plan(s).bytes;
   if (need > kScratchBytes) return SA_ERR_SCRATCH;
   void* ws = nullptr;
   int r = current_device_scratch(&ws);

@@ -1,7 +1,7 @@
-// Generic HIP path: correct for every supported dtype, head_dim and window
-// pair, written for clarity rather than speed. It serves shapes the MFMA
-// kernels do not specialise (fp32 data, w2 not a multiple of 32, small
-// head_dim) and is the fallback the fast paths are tested against.
+// Plain kernels, written for clarity rather than speed: the determinant logits
+// outside the bf16 kernels' shapes, and the trilinear query-side gradients with
+// w2 > 128 (the other float32 and small shapes run in f32.hip). Also Delta for
+// all of them.
 //
 // One workgroup of 256 threads owns one output row. Threads stride over the
 // (j, k) pairs of that row, each keeping a private D-vector accumulator in
@@ -215,18 +215,26 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(Shape s, const T* __restr
 }
 
 // ------------------------------------------------------------------ delta ---
-template <typename T>
-__global__ void delta_kernel(Shape s, const T* __restrict__ out, const T* __restrict__ dout,
-                             float* __restrict__ delta) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+// D / 4 lanes per query row, four elements each.
+template <typename T, int D>
+__global__ __launch_bounds__(kThreads) void delta_kernel(Shape s, const T* __restrict__ out,
+                                                         const T* __restrict__ dout,
+                                                         float* __restrict__ delta) {
+  constexpr int LPR = D / 4;
+  const int64_t idx = (static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x) / LPR;
+  const int part = threadIdx.x % LPR;
   const int64_t total = static_cast<int64_t>(s.B) * s.H * s.N;
-  if (idx >= total) return;
-  const int i = static_cast<int>(idx % s.N);
-  const int bh = static_cast<int>(idx / s.N);
-  const size_t off = ((static_cast<size_t>(bh / s.H) * s.N + i) * s.H + bh % s.H) * s.D;
   float acc = 0.f;
-  for (int d = 0; d < s.D; ++d) acc += ld(out + off + d) * ld(dout + off + d);
-  delta[idx] = acc;
+  if (idx < total) {
+    const int i = static_cast<int>(idx % s.N);
+    const int bh = static_cast<int>(idx / s.N);
+    const size_t off = ((static_cast<size_t>(bh / s.H) * s.N + i) * s.H + bh % s.H) * D + 4 * part;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc += ld(out + off + e) * ld(dout + off + e);
+  }
+#pragma unroll
+  for (int off = LPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  if (idx < total && part == 0) delta[idx] = acc;
 }
 
 // --------------------------------------------------------------------- dQ ---
@@ -338,22 +346,15 @@ __global__ __launch_bounds__(kThreads) void keyside_kernel(
   if (threadIdx.x < D) st(grad + rows.at(r) + threadIdx.x, MODE == 0 ? g * s.scale : g);
 }
 
-template <typename T, int D, int FORM>
-hipError_t fwd_f(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
+template <typename T, int D>
+hipError_t fwd_t(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
                  const void* vp, void* out, float* lse, hipStream_t st) {
   const unsigned grid = static_cast<unsigned>(s.N) * s.B * s.H;
-  hipLaunchKernelGGL((fwd_kernel<T, D, FORM>), dim3(grid), dim3(kThreads), 0, st, s,
+  hipLaunchKernelGGL((fwd_kernel<T, D, 1>), dim3(grid), dim3(kThreads), 0, st, s,
                      static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(kp),
                      static_cast<const T*>(v), static_cast<const T*>(vp), static_cast<T*>(out),
                      lse);
   return hipGetLastError();
-}
-
-template <typename T, int D>
-hipError_t fwd_t(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
-                 const void* vp, void* out, float* lse, hipStream_t st) {
-  return s.form == 0 ? fwd_f<T, D, 0>(s, q, k, kp, v, vp, out, lse, st)
-                     : fwd_f<T, D, 1>(s, q, k, kp, v, vp, out, lse, st);
 }
 
 template <typename T, int D, int FORM>
@@ -368,11 +369,13 @@ hipError_t bwd_stage_f(const Shape& s, BwdStage stage, const T* q, const T* k, c
                        kp, k, vp, v, dout, lse, delta, static_cast<T*>(g1));
     hipLaunchKernelGGL((keyside_kernel<T, D, 1, 1, FORM>), dim3(grid), dim3(kThreads), 0, st, s, q,
                        kp, k, vp, v, dout, lse, delta, static_cast<T*>(g2));
-  } else {
+  } else if constexpr (FORM == 1) {
     hipLaunchKernelGGL((keyside_kernel<T, D, 0, 0, FORM>), dim3(grid), dim3(kThreads), 0, st, s, q,
                        k, kp, v, vp, dout, lse, delta, static_cast<T*>(g0));
     hipLaunchKernelGGL((keyside_kernel<T, D, 0, 1, FORM>), dim3(grid), dim3(kThreads), 0, st, s, q,
                        k, kp, v, vp, dout, lse, delta, static_cast<T*>(g1));
+  } else {
+    return hipErrorInvalidValue;  // the trilinear key side is f32.hip's for every shape
   }
   return hipGetLastError();
 }
@@ -403,6 +406,7 @@ hipError_t bwd_stage_t(const Shape& s, BwdStage stage, const void* q_, const voi
     default: return hipErrorInvalidValue;     \
   }
 
+// Determinant logits only.
 hipError_t generic_fwd(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
                        const void* vp, void* out, float* lse, hipStream_t st) {
   if (s.dtype == 0) {
@@ -411,19 +415,20 @@ hipError_t generic_fwd(const Shape& s, const void* q, const void* k, const void*
   SA_DISPATCH_D(uint16_t, fwd_t, s, q, k, kp, v, vp, out, lse, st);
 }
 
+template <typename T, int D>
+static hipError_t delta_go(const Shape& s, const void* out, const void* dout, float* delta, hipStream_t st) {
+  const int64_t threads = static_cast<int64_t>(s.B) * s.H * s.N * (D / 4);
+  hipLaunchKernelGGL((delta_kernel<T, D>), dim3(static_cast<unsigned>((threads + kThreads - 1) / kThreads)),
+                     dim3(kThreads), 0, st, s, static_cast<const T*>(out), static_cast<const T*>(dout), delta);
+  return hipGetLastError();
+}
+
 hipError_t launch_delta(const Shape& s, const void* out, const void* dout, float* delta,
                         hipStream_t st) {
-  const int64_t total = static_cast<int64_t>(s.B) * s.H * s.N;
-  const unsigned grid = static_cast<unsigned>((total + 255) / 256);
   if (s.dtype == 0) {
-    hipLaunchKernelGGL(delta_kernel<float>, dim3(grid), dim3(256), 0, st, s,
-                       static_cast<const float*>(out), static_cast<const float*>(dout), delta);
-  } else {
-    hipLaunchKernelGGL(delta_kernel<uint16_t>, dim3(grid), dim3(256), 0, st, s,
-                       static_cast<const uint16_t*>(out), static_cast<const uint16_t*>(dout),
-                       delta);
+    SA_DISPATCH_D(float, delta_go, s, out, dout, delta, st);
   }
-  return hipGetLastError();
+  SA_DISPATCH_D(uint16_t, delta_go, s, out, dout, delta, st);
 }
 
 hipError_t generic_bwd_stage(const Shape& s, BwdStage stage, const void* q, const void* k,

@@ -48,7 +48,8 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
   return static_cast<uint16_t>(u >> 16);
 }
 
-// ---- generic path (any supported dtype / head_dim / windows) --------------
+// ---- plain kernels (generic.hip): determinant logits of any dtype, head_dim and
+// windows; of the trilinear backward the query side ----
 hipError_t generic_fwd(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
                        const void* vp, void* out, float* lse, hipStream_t st);
 // The backward is split into a query-side stage (dQ, dK', dV') and a key-side
@@ -58,6 +59,27 @@ hipError_t generic_bwd_stage(const Shape& s, BwdStage stage, const void* q, cons
                              const void* kp, const void* v, const void* vp, const void* dout,
                              const float* lse, const float* delta, void* g0, void* g1, void* g2,
                              hipStream_t st);
+
+// ---- float32 arithmetic on the matrix cores (f32.hip; trilinear logits) ----
+hipError_t f32_fwd(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
+                   const void* vp, void* out, float* lse, hipStream_t st);
+// Work split of its backward and workspace: Delta ([B, H, N] floats), then from
+// halo_off the query side's partial dk' / dv' rows (halo_floats per array: head /
+// tail x dk' / dv' as in BwdPlan, or, `full`, dk' and dv' of every k-row a chunk
+// touches; none with one chunk per head) and, key_floats further, the key side's
+// partial sums ([ks, 2, B*H, N, D], ks > 1 only).
+struct F32Plan {
+  int lw, groups, W2T, qs, CQ, nchunks, ks;
+  bool full;
+  size_t halo_floats, key_floats, halo_off, bytes;
+};
+F32Plan f32_bwd_plan(const Shape& s);
+// Whether its query side takes the shape (its key side takes every one).
+bool f32_bwd_query_supported(const Shape& s);
+hipError_t f32_bwd_stage(const Shape& s, BwdStage stage, const void* q, const void* k,
+                         const void* kp, const void* v, const void* vp, const void* dout,
+                         const float* lse, const float* delta, void* g0, void* g1, void* g2,
+                         float* halo, hipStream_t st);
 
 // ---- gfx950 MFMA path (bf16, head_dim 64/128, w2 <= 64) --------------------
 bool mfma_fwd_supported(const Shape& s);

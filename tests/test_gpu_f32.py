@@ -1,0 +1,119 @@
+"""GPU tests of the float32 MFMA kernels (float32 data; bf16 with head_dim 16 / 32
+or w2 > 64) against the oracle, at the edges of their row packing, key blocks,
+query chunks and workspace splits, and with infinities and NaN in the inputs."""
+
+import pytest
+import torch
+
+import parity as P
+from paper_2507_02754_amd import (load_library, simplicial_attn_bwd, simplicial_attn_bwd_noalloc,
+                                  simplicial_attn_bwd_workspace_size, simplicial_attn_fwd,
+                                  simplicial_attn_path_name)
+from paper_2507_02754_amd.workloads import draw
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    load_library()
+
+
+SHAPES = [
+    # (B, H, N, D, w1, w2, dtype): 8, 4, 2 and 1 queries per wavefront, one to
+    # four row groups, chunks longer and shorter than the k-row window
+    (1, 1, 1, 16, 1, 1, "fp32"),
+    (1, 2, 70, 16, 31, 8, "fp32"),
+    (2, 1, 97, 32, 33, 9, "fp32"),
+    (1, 1, 130, 64, 64, 16, "fp32"),
+    (1, 2, 101, 128, 32, 17, "fp32"),
+    (1, 1, 75, 128, 1, 32, "fp32"),      # w1 = 1: one key per query
+    (1, 1, 90, 64, 500, 33, "fp32"),     # w1 past the sequence
+    (1, 1, 140, 32, 50, 96, "fp32"),     # three row groups
+    (1, 1, 150, 16, 40, 127, "fp32"),
+    (1, 1, 160, 128, 20, 128, "fp32"),
+    (1, 1, 150, 64, 24, 129, "fp32"),    # query side on the plain kernels
+    (1, 1, 70, 128, 64, 65, "bf16"),
+    (1, 2, 131, 32, 100, 16, "bf16"),
+    (1, 1, 33, 16, 32, 32, "bf16"),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[str(s) for s in SHAPES])
+def test_f32_kernels_against_oracle(shape):
+    b, h, n, d, w1, w2, dt = shape
+    dtype = torch.float32 if dt == "fp32" else torch.bfloat16
+    assert simplicial_attn_path_name(0, b, n, h, d, w1, w2, dtype) == "generic"
+    print(f"\n[f32] {shape}", flush=True)
+    inputs = draw((b, n, h, d), seed=n + d + w2, dtype=dtype)
+    scale = d ** -0.5
+    o, lse = P.gpu_forward(inputs, w1, w2, scale)
+    grads = P.gpu_backward(inputs, o, lse, w1, w2, scale)
+    o_ref, lse_ref, g_ref = P.full_oracle(inputs, w1, w2, scale)
+    P.check_forward(P.to64(o), P.to64(lse), o_ref, lse_ref, dt, str(shape))
+    if w1 == 1 and min(n, w2) == 1:
+        # one pair per query: dQ, dK, dK' vanish in exact arithmetic; what is left
+        # is the rounding of dP - Delta (D terms each) times a unit-scale operand
+        bound = 64 * 2.0 ** -24 * d ** 0.5
+        assert all(float(g.abs().max()) <= bound for g in grads[:3])
+        P.check_grads([P.to64(g) for g in grads[3:]], g_ref[3:], dt, str(shape))
+    else:
+        P.check_grads([P.to64(g) for g in grads], g_ref, dt, str(shape))
+
+
+@pytest.mark.parametrize("h,n,d,w2", [(1, 300, 64, 16), (16, 640, 32, 32), (1, 257, 32, 128), (40, 520, 16, 8)])
+def test_f32_splits_agree(h, n, d, w2):
+    """Few and many workgroups take different chunk lengths and key-side splits;
+    the allocation-free entry (its workspace capped at 64 MiB) runs the same
+    split where it fits. Run twice: bitwise the same."""
+    w1 = 70
+    print(f"\n[f32] splits H={h} N={n} D={d} w2={w2}", flush=True)
+    x = [t.cuda() for t in draw((1, n, h, d), seed=5 + n, dtype=torch.float32)]
+    o, lse = simplicial_attn_fwd(*x[:5], w1, w2)
+    ref = simplicial_attn_bwd(*x[:5], o, x[5], lse, w1, w2)
+    again = simplicial_attn_bwd(*x[:5], o, x[5], lse, w1, w2)
+    noalloc = simplicial_attn_bwd_noalloc(*x[:5], o, x[5], lse, w1, w2)
+    torch.cuda.synchronize()
+    fits = simplicial_attn_bwd_workspace_size(1, n, h, d, w1, w2, torch.float32) <= 64 << 20
+    for a, c, e in zip(ref, again, noalloc):
+        assert torch.equal(a, c)
+        assert torch.equal(a, e) if fits else torch.allclose(a, e, rtol=1e-4, atol=1e-5)
+    one = [t[:, :, :1].contiguous() for t in x]  # head 0 alone: fewer workgroups
+    o1, lse1 = simplicial_attn_fwd(*one[:5], w1, w2)
+    g1 = simplicial_attn_bwd(*one[:5], o1, one[5], lse1, w1, w2)
+    torch.cuda.synchronize()
+    for a, c in zip(ref, g1):
+        # the same sums in another order: a few hundred float32 additions
+        assert float((a[:, :, :1] - c).abs().max()) <= 1e-5 * float(c.abs().max())
+
+
+@pytest.mark.parametrize("w2,d", [(5, 64), (16, 128), (16, 16), (32, 32)])
+def test_f32_rows_outside_the_window_do_not_matter(w2, d):
+    """Infinities and NaN in one row of K / V (or of dO, K', V', Q) reach only the
+    outputs whose windows include that row: everything else is finite and agrees
+    with the run on clean inputs."""
+    n, w1, r = 150, 40, 77
+    x = [t.cuda() for t in draw((1, n, 1, d), seed=w2 + d, dtype=torch.float32)]
+    o, lse = simplicial_attn_fwd(*x[:5], w1, w2)
+    g = simplicial_attn_bwd(*x[:5], o, x[5], lse, w1, w2)
+    idx = torch.arange(n, device="cuda")
+    for t, name in enumerate(("q", "k", "kp", "v", "vp", "do")):
+        print(f"\n[f32] non-finite row in {name} w2={w2} D={d}", flush=True)
+        y = [z.clone() for z in x]
+        y[t][0, r, 0, :3] = torch.tensor([float("inf"), float("nan"), -float("inf")], device="cuda")
+        win = {"k": w1, "v": w1, "kp": w2, "vp": w2}.get(name, 1)
+        seen = (idx >= r) & (idx < r + win)  # queries that read the row
+        o2, l2 = simplicial_attn_fwd(*y[:5], w1, w2)
+        g2 = simplicial_attn_bwd(*y[:5], o, y[5], lse, w1, w2)  # clean O, LSE: the operands alone
+        torch.cuda.synchronize()
+        assert torch.allclose(o2[0, ~seen], o[0, ~seen], rtol=1e-4, atol=1e-5), name
+        assert torch.allclose(l2[0, :, ~seen], lse[0, :, ~seen], rtol=1e-4, atol=1e-5), name
+        qs = torch.nonzero(seen).flatten()
+        lo, hi = int(qs.min()), int(qs.max())
+        reach = {0: ~seen,
+                 1: (idx <= lo - w1) | (idx > hi), 3: (idx <= lo - w1) | (idx > hi),
+                 2: (idx <= lo - w2) | (idx > hi), 4: (idx <= lo - w2) | (idx > hi)}
+        for gi, keep in reach.items():
+            assert torch.allclose(g2[gi][0, keep], g[gi][0, keep], rtol=1e-4, atol=1e-5), (name, gi)
