@@ -231,18 +231,31 @@ __global__ __launch_bounds__(64 * WAVES) void bwd_q_kernel(
   }
 
   // ---- K/V blocks: one pipeline over (query tile, 32-key block) ----
-  // stage_fetch loads this wavefront's share of block `it` into registers
+  // stage_fetch loads this wavefront's share of the next block into registers
   // (16 bytes per lane per load, the chunk that belongs at LDS offset
   // 1024 k + 16 lane of the swizzled tile); stage_put writes it into a stage
   // one block later.
-  const int nb = (w1 + QW - 1 + 31) / 32;
+  // A tile's key window union starts at max(0, i0 - w1 + 1): the first tiles of
+  // a head walk only the blocks that hold keys.
   const int ntiles = (ce - cs + QW - 1) / QW;
-  const int total_it = ntiles * nb;
+  auto tile_jlo = [&](int i0) { return max(i0 - w1 + 1, 0); };
+  auto tile_nb = [&](int i0) { return (i0 + QW - 1 - tile_jlo(i0) + 32) / 32; };
+  int total_it = ntiles * tile_nb(cs);
+  if (cs < w1 - 1) {
+    total_it = 0;
+    for (int i0 = cs; i0 < ce; i0 += QW) total_it += tile_nb(i0);
+  }
+  int f_i0 = cs, f_jb = tile_jlo(cs), f_left = tile_nb(cs);  // next block to load: tile, first key, blocks left
   constexpr int SPW = (T::instrs + WAVES - 1) / WAVES;
   u32x4_t skr[SPW], svr[SPW];
-  auto stage_fetch = [&](int it) {
-    const int tile = it / nb, blk = it - tile * nb;
-    const int jb = cs + tile * QW - w1 + 1 + 32 * blk;
+  auto stage_fetch = [&]() {
+    const int jb = f_jb;
+    f_jb += 32;
+    if (--f_left == 0) {
+      f_i0 += QW;
+      f_jb = tile_jlo(f_i0);
+      f_left = tile_nb(f_i0);
+    }
 #pragma unroll
     for (int x = 0; x < SPW; ++x) {
       const int kx = x * WAVES + wave;
@@ -265,14 +278,14 @@ __global__ __launch_bounds__(64 * WAVES) void bwd_q_kernel(
   };
   // Blocks 0 and 1 go into the two stages, block 2 into the registers.
   if (total_it > 0) {
-    stage_fetch(0);
+    stage_fetch();
     stage_put(smem);
   }
   if (total_it > 1) {
-    stage_fetch(1);
+    stage_fetch();
     stage_put(smem + L::stageBytes);
   }
-  if (total_it > 2) stage_fetch(2);
+  if (total_it > 2) stage_fetch();
   float nlse = lse[stat + min(cs + qs, N - 1)], ndlt = delta[stat + min(cs + qs, N - 1)];
   lds_barrier();  // acc ring cleared, first rows and blocks 0, 1 in LDS
 
@@ -336,10 +349,10 @@ __global__ __launch_bounds__(64 * WAVES) void bwd_q_kernel(
     // epilogue uses the freed stage for the dq sums.
     // The products start from loop-invariant accumulator tiles: S from
     // -lse2 (the logits come out already normalised) and dP from -Delta.
-    const int jlo = i0 - w1 + 1;
+    const int jlo = tile_jlo(i0), nb = tile_nb(i0);
     if (tile > 0) {
       if (it + 1 < total_it) stage_put(smem + ((it + 1) & 1) * L::stageBytes);
-      if (it + 2 < total_it) stage_fetch(it + 2);
+      if (it + 2 < total_it) stage_fetch();
     }
     lds_barrier();
     f32x16_t c_s, c_dp;
@@ -373,8 +386,8 @@ __global__ __launch_bounds__(64 * WAVES) void bwd_q_kernel(
       const char* kt = smem + S * L::stageBytes;
       const char* vt = kt + T::bytes;
       // Keys of this block inside query i's window and inside [0, N).
-      const int lo = max(qs, -jlo) - 32 * blk;
-      const int hi = min(qs + w1 - 1, N - 1 - jlo) - 32 * blk;
+      const int lo = max(i - w1 + 1 - jlo, 0) - 32 * blk;
+      const int hi = min(i, N - 1) - jlo - 32 * blk;
       const bool edge = lo > 0 || hi < 31;
 
       // (A) dP^T - Delta = V do~^T - Delta, overlapped with the
@@ -444,7 +457,7 @@ __global__ __launch_bounds__(64 * WAVES) void bwd_q_kernel(
       if (blk + 1 < nb) {
         lds_barrier();
         if (it + 2 < total_it) stage_put(smem + S * L::stageBytes);
-        if (it + 3 < total_it) stage_fetch(it + 3);
+        if (it + 3 < total_it) stage_fetch();
         __builtin_amdgcn_sched_barrier(0);
         logits(smem + (S ^ 1) * L::stageBytes);
         __builtin_amdgcn_sched_barrier(0);

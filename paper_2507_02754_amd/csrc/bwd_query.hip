@@ -182,20 +182,28 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
   // Wavefronts w < F::instrs move the K and V tiles of a block, 16 bytes per
   // lane, into the fragment-major layout; block `it` goes into stage it % NS.
   using F = FragTile<D>;
-  const int nb = (w1 + QW - 1 + 31) / 32;
+  // A tile's key window union starts at max(0, i0 - w1 + 1): the first tiles of
+  // a head walk only the blocks that hold keys.
   const int ntiles = (ce - cs + QW - 1) / QW;
-  const int total_it = ntiles * nb;
+  auto tile_jlo = [&](int i0) { return max(i0 - w1 + 1, 0); };
+  auto tile_nb = [&](int i0) { return (i0 + QW - 1 - tile_jlo(i0) + 32) / 32; };
   const __amdgpu_buffer_rsrc_t rk = make_rsrc(k + basek, hbk), rv = make_rsrc(v + basek, hbk);
   const bool stager = wave < F::instrs;
   const int st_row = (64 * wave + lane) / F::CH, st_ch = (64 * wave + lane) % F::CH;
   const int st_slot = F::slot(st_row, st_ch);
   u32x4_t skr = {0u, 0u, 0u, 0u}, svr = {0u, 0u, 0u, 0u};
-  auto stage_fetch = [&](int it) {
-    const int tile = it / nb, blk = it - tile * nb;
-    const int jb = cs + tile * QW - w1 + 1 + 32 * blk;
-    const int off = stager && it < total_it ? (jb + st_row) * rsbk + 16 * st_ch : -1;
+  // Loads the next block of the (tile, block) sequence.
+  int f_i0 = cs, f_jb = tile_jlo(cs), f_left = tile_nb(cs);  // its tile, first key, blocks left in the tile
+  auto stage_fetch = [&]() {
+    const int off = stager && f_i0 < ce ? (f_jb + st_row) * rsbk + 16 * st_ch : -1;
     skr = ldbuf128(rk, off);
     svr = ldbuf128(rv, off);
+    f_jb += 32;
+    if (--f_left == 0) {
+      f_i0 += QW;
+      f_jb = tile_jlo(f_i0);
+      f_left = tile_nb(f_i0);
+    }
   };
   auto stage_put = [&](int it) {
     if (stager) {
@@ -205,11 +213,11 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
     }
   };
   // Blocks 0 and 1 into their stages, block 2 into the registers.
-  stage_fetch(0);
+  stage_fetch();
   stage_put(0);
-  stage_fetch(1);
+  stage_fetch();
   stage_put(1);
-  stage_fetch(2);
+  stage_fetch();
 
   // ---- per-lane LDS bases of the operand fragments (fragment-major tiles) ----
   const int rbase0 = F::row_base(lane, 0), rbase1 = F::row_base(lane, 1);
@@ -234,7 +242,7 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
   // into the registers.
   auto stage_step = [&](int it) {
     stage_put(it + 2);
-    stage_fetch(it + 3);
+    stage_fetch();
   };
   // Rows that no later query of the chunk touches are complete.
   auto flush_tile = [&](int i0) {
@@ -303,7 +311,7 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
       const int kk = i - W2P + 1 + c;
       const bool qvalid = i < ce;
       const bool rowvalid = qvalid && kk >= 0 && kk > i - w2;
-      const int jlo = i0 - w1 + 1;
+      const int jlo = tile_jlo(i0), nb = tile_nb(i0);
       // Rows outside the window get an infinite normaliser: P = 0.
       const float lse2 = rowvalid ? st_cur * kLog2e : __builtin_inff();
       if (tile + 1 < ntiles) st_cur = lse[stat + min(i + QW, N - 1)];  // next tile's, ahead of use
@@ -361,8 +369,8 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
         f32x16_t sacc = mfma32(ka[0], qt[0], f32x16_t{});
 #pragma unroll
         for (int t = 1; t < NT; ++t) sacc = mfma32(ka[t], qt[t], sacc);
-        const int lo = max(qs, -jlo) - 32 * blk;
-        const int hi = min(qs + w1 - 1, N - 1 - jlo) - 32 * blk;
+        const int lo = max(i - w1 + 1 - jlo, 0) - 32 * blk;
+        const int hi = min(i, N - 1) - jlo - 32 * blk;
         float pr[16];
 #pragma unroll
         for (int vv = 0; vv < 16; ++vv) pr[vv] = fast_exp2(sacc[vv] - lse2);
@@ -447,6 +455,7 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
       const bool qvalid = i < ce;
       const bool rowvalid = qvalid && kk >= 0 && kk > i - w2;
       const float dlt = qvalid ? st_cur : 0.f;
+      const int nb = tile_nb(i0);
       if (tile + 1 < ntiles) st_cur = delta[stat + min(i + QW, N - 1)];  // next tile's, ahead of use
       const u32x4_t nrow = row_load(rowloader && tile + 1 < ntiles ? i0 + QW : -RL - 1);
       const int kslot = (kk - kbase) % RK;
