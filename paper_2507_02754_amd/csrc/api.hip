@@ -6,6 +6,7 @@
 #include <limits.h>
 #include <math.h>
 
+#include <algorithm>
 #include <initializer_list>
 #include <mutex>
 
@@ -112,14 +113,19 @@ GqaLayout gqa_layout(int64_t B, int64_t N, int64_t H, int64_t Hkv, int64_t D, in
   GqaLayout l{0, 0, 0};
   if (check_sizes(B, N, H, D, w1, w2, dtype) != SA_OK) return l;
   if (Hkv <= 0 || Hkv > H || H % Hkv != 0) return l;
-  l.base = (workspace_bytes_for(B, N, H, D, w1, w2, dtype) + 255) & ~size_t(255);
   if (Hkv == H) {
     l.bytes = workspace_bytes_for(B, N, H, D, w1, w2, dtype);
     return l;
   }
   const size_t esize = dtype == SA_DTYPE_BF16 ? 2 : 4;
   l.per_tensor = (static_cast<size_t>(B * N * H * D) * esize + 255) & ~size_t(255);
-  const bool native = gqa_native(make_shape(B, N, H, D, w1, w2, 1.0f, dtype));
+  Shape s = make_shape(B, N, H, D, w1, w2, 1.0f, dtype);
+  const bool native = gqa_native(s);
+  s.Hkv = static_cast<int>(Hkv);
+  // (the grouped plan may split its fewer key blocks further)
+  l.base = workspace_bytes_for(B, N, H, D, w1, w2, dtype);
+  if (native) l.base = std::max(l.base, sa::mfma_bwd_plan(s).bytes);
+  l.base = (l.base + 255) & ~size_t(255);
   l.bytes = l.base + (native ? 2 : 8) * l.per_tensor;
   return l;
 }
@@ -348,7 +354,8 @@ size_t simplicial_attn_bwd_fused_workspace_size(int64_t B, int64_t N, int64_t H,
                                                 int32_t w2, int32_t dtype) {
   if (check_sizes(B, N, H, D, w1, w2, dtype) != SA_OK) return 0;
   const Shape s = make_shape(B, N, H, D, w1, w2, 1.0f, dtype);
-  return fused_path(s) ? sa::mfma_fused_plan(s).bytes : 0;
+  // The preprocess stage asks for the split backward's workspace.
+  return fused_path(s) ? std::max(sa::mfma_fused_plan(s).bytes, sa::mfma_bwd_plan(s).bytes) : 0;
 }
 
 // Validation shared by the fused entry points.
@@ -471,7 +478,7 @@ int simplicial_attn_bwd_gqa(const void* q, const void* k, const void* kp, const 
   if (check_ptrs({q, k, kp, v, vp, out, dout, lse, dq, dk, dkp, dv, dvp, workspace}) != SA_OK)
     return SA_ERR_INVALID;
   if (Hkv <= 0 || Hkv > H || H % Hkv != 0) return SA_ERR_INVALID;
-  const int rc = check_bwd(B, N, H, D, w1, w2, scale, dtype, workspace_bytes);
+  const int rc = check_bwd(B, N, H, D, w1, w2, scale, dtype, SIZE_MAX);
   if (rc != SA_OK) return rc;
   const GqaLayout l = gqa_layout(B, N, H, Hkv, D, w1, w2, dtype);
   if (workspace_bytes < l.bytes) return SA_ERR_WORKSPACE;

@@ -97,15 +97,17 @@ using ic = std::integral_constant<int, X>;
 // FORM 1: determinant logits (Section 5): role A forms q~ = k'_k x q_i per
 // 3-component chunk (unscaled), so S = q~ K^T is the determinant logit and
 // dK = scale sum_r dS_rj q~_r as for the trilinear form.
+// SPLIT: a key block's row blocks are shared out to ks > 1 workgroups (its own
+// instantiation: a run that starts at a known 0 compiles 2.5% faster).
 // GQ: grouped-query attention with fewer K-side heads than query heads (the
 // workgroup walks several query heads' row blocks); otherwise one query head
 // per K-side head, with no group indexing in the loop.
-template <int D, int G, bool BIAS, int FORM, bool FUSED, bool GQ>
+template <int D, int G, bool BIAS, int FORM, bool FUSED, bool GQ, bool SPLIT>
 __device__ __forceinline__ void key_body(
     Shape s, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ kp, const uint16_t* __restrict__ v, const uint16_t* __restrict__ vp,
     const uint16_t* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
-    uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, FusedPlan fp, float* __restrict__ part) {
+    uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, FusedPlan fp, int ks, float* __restrict__ part) {
   constexpr int NT = D / 16, NDT = D / 32;
   constexpr int W2P = 32 * G;
   static_assert(!FUSED || (G == 1 && FORM == 0 && !GQ), "fused backward: w2 <= 32, trilinear logits, Hkv = H");
@@ -121,13 +123,18 @@ __device__ __forceinline__ void key_body(
   // walks the row blocks of its QG query heads hk QG .. hk QG + QG - 1 in turn
   // (dK, dV accumulate over all of them).
   const int Hkv = GQ ? s.Hkv : s.H, QG = GQ ? s.H / s.Hkv : 1;
+  // Where there are few key blocks the row blocks of one go to ks workgroups
+  // (each a run of the sequence of all heads' row blocks), whose float32 sums
+  // key_sum_kernel adds in order.
   const int jblocks = (s.N + KW - 1) / KW;
-  const int total = jblocks * s.B * Hkv;
+  if constexpr (!SPLIT) ks = 1;
+  const int total = jblocks * s.B * Hkv * ks;
   const int per_xcd = (total + 7) / 8;
   const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (logical >= total) return;
-  const int bk = logical / jblocks;
-  const int jblk = logical - bk * jblocks;
+  const int split = logical % ks;
+  const int bk = logical / ks / jblocks;
+  const int jblk = logical / ks - bk * jblocks;
   const int b = bk / Hkv, hk = bk - b * Hkv;
   const int bh = b * s.H + hk * QG;  // (batch, first query head)
 
@@ -236,12 +243,17 @@ __device__ __forceinline__ void key_body(
   unsigned frw[2][2], fmw[2][IPT][2];
   const float mbias = roleA ? s.kp_bias : s.vp_bias;
   // Row blocks of a workgroup: those of query head 0 of the group, padded to
-  // nrb4, then those of head 1, ... (R = hg nrb4 + rb = hgb + rb). The steps
+  // nrb4, then those of head 1, ... (R = hg nrb4 + rb). The steps
   // take the local rb of head hg; loc / hof map rb + k (k <= 4, possibly past
   // the end of head hg) to its local index and head. Only the guarded steps
   // (cross: std::true_type) reach past the end of a head: the straight-line
   // ones end 4 row blocks before nrb4.
-  int hg = 0, hgb = 0;
+  // This workgroup's run of R: [Ra, Rb), in whole unrolled iterations.
+  const int quads = QG * (nrb4 / kSlots), quads_per = SPLIT ? (quads + ks - 1) / ks : quads;
+  const int Ra = SPLIT ? min(split * quads_per, quads) * kSlots : 0;
+  const int Rb = SPLIT ? min((split + 1) * quads_per, quads) * kSlots : quads * kSlots;
+  const int hg0 = GQ && SPLIT ? Ra / nrb4 : 0, ra = Ra - hg0 * nrb4;  // head and local index of Ra
+  int hg = hg0, hgq = hg0 * (nrb4 / kSlots);  // hgq: R of the head's first row block / 4
   auto loc = [&](int r, auto cross) {
     if constexpr (!GQ || !decltype(cross)::value)
       return r;
@@ -330,7 +342,7 @@ __device__ __forceinline__ void key_body(
   // Per-row-block statistic, 64 row blocks at a time: lane l holds the value
   // of row block (R & ~63) + l (A: -LSE * log2 e, B: Delta), taken with a
   // lane read. The next 64 values are loaded half a window ahead. stat_at
-  // must be called for every row block in order (R = hg nrb4 + rb).
+  // must be called for every row block of the run in order (R = hg nrb4 + rb).
   const float* statp = roleA ? lse : delta;
   auto stat_load = [&](int rb0) {  // rb0: R of the first of 64 row blocks
     const int rg = rb0 + lane, hq = GQ ? rg / nrb4 : 0;
@@ -338,10 +350,10 @@ __device__ __forceinline__ void key_body(
     const float x = statp[stat + static_cast<size_t>(min(hq, QG - 1)) * N + ii];
     return roleA ? -x * kLog2e : x;
   };
-  float st_l = stat_load(0), st_nx = 0.f;
+  float st_l = stat_load(Ra & ~63), st_nx = stat_load((Ra & ~63) + 64);
   auto stat_at = [&](int rb) {
     if ((rb & 63) == 32) st_nx = stat_load((rb & ~63) + 64);
-    if ((rb & 63) == 0 && rb > 0) st_l = st_nx;
+    if ((rb & 63) == 0 && rb > Ra) st_l = st_nx;
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, st_l), rb & 63));
   };
   // Keys of this group inside query i's window and the sequence, for a real row block.
@@ -380,12 +392,12 @@ __device__ __forceinline__ void key_body(
   }
   // tiles 0 and 1 (fused: role B forms the do~ halves, role C the q~ halves)
   if (FUSED ? role == 1 : true) {
-    fetch(0, ic<0>{}, std::false_type{});
+    fetch(ra, ic<0>{}, std::false_type{});
     form_put(0, ic<0>{});
-    fetch(1, ic<0>{}, std::false_type{});
+    fetch(ra + 1, ic<0>{}, std::false_type{});
     form_put(L::tileBytes, ic<0>{});
-    fetch(2, ic<0>{}, std::false_type{});
-    if (roleA) fetch(3, ic<1>{}, std::false_type{});
+    fetch(ra + 2, ic<0>{}, std::false_type{});
+    if (roleA) fetch(ra + 3, ic<1>{}, std::false_type{});
   }
   // The loops start with every load complete (the wait-count pass would
   // otherwise keep the K/V operand loads pending into every iteration).
@@ -400,6 +412,9 @@ __device__ __forceinline__ void key_body(
   int rb_hi = min((w1 + 30) * G - 1, min(nrb - 1, (N - j0) * G - 1));
   rb_hi = rb_hi / kSlots * kSlots;
   if (j0 + 32 * (NKG - 1) >= N || rb_hi < rb_lo) rb_lo = rb_hi = nrb4;
+  // A step's refill of the statistics must fold away in three of the four steps:
+  // where it stayed a branch in each (rb % 4 not known at compile time) the
+  // straight-line quad fell into four blocks and the key side was 14% slower.
   auto run_loops = [&](auto& step) __attribute__((always_inline)) {
     auto quad = [&](int rb, auto guard) __attribute__((always_inline)) {
       step(rb, ic<0>{}, guard);
@@ -407,11 +422,23 @@ __device__ __forceinline__ void key_body(
       step(rb + 2, ic<2>{}, guard);
       step(rb + 3, ic<3>{}, guard);
     };
-    for (hg = 0, hgb = 0; hg < QG; ++hg, hgb += nrb4) {
-      int rb = 0;
-      for (; rb < rb_lo; rb += kSlots) quad(rb, ic<1>{});
-      for (; rb < rb_hi; rb += kSlots) quad(rb, ic<0>{});
-      for (; rb < nrb4; rb += kSlots) quad(rb, ic<1>{});
+    if constexpr (!SPLIT) {
+      for (hg = 0, hgq = 0; hg < QG; ++hg, hgq += nrb4 / kSlots) {
+        int rb = 0;
+        for (; rb < rb_lo; rb += kSlots) quad(rb, ic<1>{});
+        for (; rb < rb_hi; rb += kSlots) quad(rb, ic<0>{});
+        for (; rb < nrb4; rb += kSlots) quad(rb, ic<1>{});
+      }
+    } else {
+      for (; hgq < Rb / kSlots; ++hg, hgq += nrb4 / kSlots) {
+        // in units of unrolled iterations, so that the compiler sees rb % 4 == 0
+        int n = max(Ra / kSlots - hgq, 0);
+        const int re = min(nrb4 / kSlots, Rb / kSlots - hgq);
+        const int r1 = min(rb_lo / kSlots, re), r2 = min(rb_hi / kSlots, re);
+        for (; n < r1; ++n) quad(n * kSlots, ic<1>{});
+        for (; n < r2; ++n) quad(n * kSlots, ic<0>{});
+        for (; n < re; ++n) quad(n * kSlots, ic<1>{});
+      }
     }
   };
 
@@ -459,8 +486,8 @@ __device__ __forceinline__ void key_body(
     u32x4_t pcur[2];  // P of the row block whose dV is next (set only when active)
     if constexpr (FUSED) lds_barrier();  // role C has formed tiles 0 and 1
     {
-      const float nl0 = stat_at(0);
-      if (is_active(0, j0)) probs(0, nl0, logits(0), 0, pcur, std::false_type{});
+      const float nl0 = stat_at(Ra);
+      if (is_active(ra, j0 + ra / G)) probs(ra, nl0, logits(0), 0, pcur, std::false_type{});
     }
     lds_barrier();
     // Iteration rb, tile slot S = rb % 4. The q~ half of tile rb + 2 is formed
@@ -475,7 +502,11 @@ __device__ __forceinline__ void key_body(
       constexpr bool kGuard = decltype(guard)::value != 0;
       const bool act0 = !kGuard || is_active(rb, j0 + rb / G);
       const bool act1 = !kGuard || is_active(loc(rb + 1, guard), j0 + loc(rb + 1, guard) / G);
-      const float nl1 = stat_at(hgb + rb + 1);
+      // (opaque: with the refills folded three steps become one block, whose
+      // schedule measured 1% slower here)
+      int rn = hgq * kSlots + rb + 1;
+      asm volatile("" : "+s"(rn));
+      const float nl1 = stat_at(rn);
       f32x16_t snext;
       u32x4_t pnext[2];
       if constexpr (!kGuard && FUSED) {
@@ -576,7 +607,7 @@ __device__ __forceinline__ void key_body(
     };
     f32x16_t dpcur;  // dP of the row block whose dK is next (set only when active)
     if constexpr (FUSED) lds_barrier();  // role C has formed tiles 0 and 1
-    if (is_active(0, j0)) dpcur = logits_dp(T::bytes);
+    if (is_active(ra, j0 + ra / G)) dpcur = logits_dp(T::bytes);
     lds_barrier();
     // dS = P (dP - Delta) of the current row block, packed (operand of dK).
     auto dsoft = [&](const u32x4_t* pf, float dlt, int uu) __attribute__((always_inline)) {
@@ -596,7 +627,7 @@ __device__ __forceinline__ void key_body(
       constexpr bool kGuard = decltype(guard)::value != 0;
       const bool act0 = !kGuard || is_active(rb, j0 + rb / G);
       const bool act1 = !kGuard || is_active(loc(rb + 1, guard), j0 + loc(rb + 1, guard) / G);
-      const float dlt = stat_at(hgb + rb);
+      const float dlt = stat_at(hgq * kSlots + rb);
       f32x16_t dpnext;
       if constexpr (!kGuard && !FUSED) {
         // Straight-line: reads first, then the dP products of row block rb + 1
@@ -933,10 +964,17 @@ __device__ __forceinline__ void key_body(
         const int j = jw + row;
         if (j < N) {
           const float* src = ob + row * L::oStride + 8 * col;
+          const size_t at = basek + static_cast<size_t>(j) * Hkv * D + 8 * col;
+          if (SPLIT) {
+            float* o = part + (2 * split + pass) * (static_cast<size_t>(s.B) * s.N * Hkv * D) + at;
+            *reinterpret_cast<float4*>(o) = *reinterpret_cast<const float4*>(src);
+            *reinterpret_cast<float4*>(o + 4) = *reinterpret_cast<const float4*>(src + 4);
+            continue;
+          }
           u32x4_t w;
 #pragma unroll
           for (int e = 0; e < 4; ++e) w[e] = pack_bf16x2(src[2 * e], src[2 * e + 1]);
-          *reinterpret_cast<u32x4_t*>(dst + basek + static_cast<size_t>(j) * Hkv * D + 8 * col) = w;
+          *reinterpret_cast<u32x4_t*>(dst + at) = w;
         }
       }
     }
@@ -944,40 +982,64 @@ __device__ __forceinline__ void key_body(
 }
 
 // The split path's key-side kernel and the fused backward kernel (one body).
-template <int D, int G, bool BIAS, int FORM, bool GQ>
+template <int D, int G, bool BIAS, int FORM, bool GQ, bool SPLIT>
 __global__ __launch_bounds__((key_threads<D, false>()), 1) void bwd_key_kernel(
     Shape s, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ kp, const uint16_t* __restrict__ v, const uint16_t* __restrict__ vp,
     const uint16_t* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
-    uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, FusedPlan fp, float* __restrict__ part) {
-  key_body<D, G, BIAS, FORM, false, GQ>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, fp, part);
+    uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, FusedPlan fp, int ks, float* __restrict__ part) {
+  key_body<D, G, BIAS, FORM, false, GQ, SPLIT>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, fp, ks, part);
 }
 template <int D, bool BIAS>
 __global__ __launch_bounds__((key_threads<D, true>()), 1) void bwd_fused_kernel(
     Shape s, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ kp, const uint16_t* __restrict__ v, const uint16_t* __restrict__ vp,
     const uint16_t* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
-    uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, FusedPlan fp, float* __restrict__ part) {
-  key_body<D, 1, BIAS, 0, true, false>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, fp, part);
+    uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, FusedPlan fp, int ks, float* __restrict__ part) {
+  key_body<D, 1, BIAS, 0, true, false, false>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, fp, 1, part);
+}
+
+// dV, dK ([B, N, Hkv, D], n elements each) from the float32 sums of the ks
+// workgroups of each key block (part: [ks][dV, dK][n]), in order.
+__global__ __launch_bounds__(256) void key_sum_kernel(size_t n, int ks, const float* __restrict__ part,
+                                                      uint16_t* __restrict__ dk, uint16_t* __restrict__ dv) {
+  const size_t at = 4 * (static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x);
+  if (at >= n) return;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    float4 a = {0.f, 0.f, 0.f, 0.f};
+    for (int p = 0; p < ks; ++p) {
+      const float4 x = *reinterpret_cast<const float4*>(part + (2 * p + t) * n + at);
+      a.x += x.x, a.y += x.y, a.z += x.z, a.w += x.w;
+    }
+    *reinterpret_cast<uint2*>((t ? dk : dv) + at) = uint2{pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w)};
+  }
 }
 
 template <int D, int G, bool BIAS, int FORM = 0, bool FUSED = false, bool GQ = false>
 hipError_t launch_key(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
                       const void* vp, const void* dout, const float* lse, const float* delta, void* dk,
-                      void* dv, hipStream_t st, const FusedPlan& fp = FusedPlan{}, float* part = nullptr) {
+                      void* dv, hipStream_t st, int ks, float* part, const FusedPlan& fp = FusedPlan{}) {
   constexpr int KW = 32 * key_groups<FUSED>();
-  const long tot = static_cast<long>((s.N + KW - 1) / KW) * s.B * s.Hkv;
-  auto kern = [] {
-    if constexpr (FUSED)
-      return bwd_fused_kernel<D, BIAS>;
-    else
-      return bwd_key_kernel<D, G, BIAS, FORM, GQ>;
-  }();
-  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(((tot + 7) / 8) * 8)), dim3(key_threads<D, FUSED>()), 0,
-                     st, s, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
-                     static_cast<const uint16_t*>(kp), static_cast<const uint16_t*>(v),
-                     static_cast<const uint16_t*>(vp), static_cast<const uint16_t*>(dout), lse, delta,
-                     static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), fp, part);
+  const long tot = static_cast<long>((s.N + KW - 1) / KW) * s.B * s.Hkv * ks;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(((tot + 7) / 8) * 8)), dim3(key_threads<D, FUSED>()), 0,
+                       st, s, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
+                       static_cast<const uint16_t*>(kp), static_cast<const uint16_t*>(v),
+                       static_cast<const uint16_t*>(vp), static_cast<const uint16_t*>(dout), lse, delta,
+                       static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), fp, ks, part);
+  };
+  if constexpr (FUSED)
+    go(bwd_fused_kernel<D, BIAS>);
+  else if (ks > 1)
+    go(bwd_key_kernel<D, G, BIAS, FORM, GQ, true>);
+  else
+    go(bwd_key_kernel<D, G, BIAS, FORM, GQ, false>);
+  if (!FUSED && ks > 1) {
+    const size_t n = static_cast<size_t>(s.B) * s.N * s.Hkv * D;
+    hipLaunchKernelGGL(key_sum_kernel, dim3(static_cast<unsigned>((n / 4 + 255) / 256)), dim3(256), 0, st, n, ks, part,
+                       static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv));
+  }
   return hipGetLastError();
 }
 
@@ -1038,25 +1100,25 @@ __global__ __launch_bounds__(256) void fused_reduce_kernel(Shape s, FusedPlan fp
 template <bool BIAS>
 hipError_t mfma_bwd_key_b(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
                           const void* vp, const void* dout, const float* lse, const float* delta,
-                          void* dk, void* dv, hipStream_t st) {
+                          void* dk, void* dv, int ks, float* part, hipStream_t st) {
   const int G = s.w2 <= 32 ? 1 : 2;
   if constexpr (!BIAS) {
     if (s.Hkv < s.H) {  // grouped-query attention (no bias constants there)
       if (s.D == 128)
-        return G == 1 ? launch_key<128, 1, false, 0, false, true>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st)
-                      : launch_key<128, 2, false, 0, false, true>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st);
+        return G == 1 ? launch_key<128, 1, false, 0, false, true>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st, ks, part)
+                      : launch_key<128, 2, false, 0, false, true>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st, ks, part);
       if (s.D == 64)
-        return G == 1 ? launch_key<64, 1, false, 0, false, true>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st)
-                      : launch_key<64, 2, false, 0, false, true>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st);
+        return G == 1 ? launch_key<64, 1, false, 0, false, true>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st, ks, part)
+                      : launch_key<64, 2, false, 0, false, true>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st, ks, part);
       return hipErrorInvalidValue;
     }
   }
   if (s.D == 128)
-    return G == 1 ? launch_key<128, 1, BIAS>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st)
-                  : launch_key<128, 2, BIAS>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st);
+    return G == 1 ? launch_key<128, 1, BIAS>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st, ks, part)
+                  : launch_key<128, 2, BIAS>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st, ks, part);
   if (s.D == 64)
-    return G == 1 ? launch_key<64, 1, BIAS>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st)
-                  : launch_key<64, 2, BIAS>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st);
+    return G == 1 ? launch_key<64, 1, BIAS>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st, ks, part)
+                  : launch_key<64, 2, BIAS>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st, ks, part);
   return hipErrorInvalidValue;
 }
 
@@ -1089,8 +1151,8 @@ hipError_t mfma_bwd_fused(const Shape& s, const void* q, const void* k, const vo
   const FusedPlan fp = mfma_fused_plan(s);
   float* ws = static_cast<float*>(workspace);
   const bool bias = s.kp_bias != 0.f || s.vp_bias != 0.f;
-  return bias ? launch_key<128, 1, true, 0, true>(s, q, k, kp, v, vp, dout, lse, ws, dk, dv, st, fp, ws)
-              : launch_key<128, 1, false, 0, true>(s, q, k, kp, v, vp, dout, lse, ws, dk, dv, st, fp, ws);
+  return bias ? launch_key<128, 1, true, 0, true>(s, q, k, kp, v, vp, dout, lse, ws, dk, dv, st, 1, ws, fp)
+              : launch_key<128, 1, false, 0, true>(s, q, k, kp, v, vp, dout, lse, ws, dk, dv, st, 1, ws, fp);
 }
 
 hipError_t mfma_bwd_fused_reduce(const Shape& s, void* dq, void* dkp, void* dvp, const void* workspace,
@@ -1109,16 +1171,16 @@ hipError_t mfma_bwd_fused_reduce(const Shape& s, void* dq, void* dkp, void* dvp,
 
 hipError_t mfma_bwd_key(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
                         const void* vp, const void* dout, const float* lse, const float* delta,
-                        void* dk, void* dv, hipStream_t st) {
+                        void* dk, void* dv, int ks, float* part, hipStream_t st) {
   const bool bias = s.kp_bias != 0.f || s.vp_bias != 0.f;
   if (s.Hkv < s.H && (s.form != 0 || bias)) return hipErrorInvalidValue;  // grouped-query: trilinear, no constants
   if (s.form == 1) {  // determinant logits: w2 <= 32, no bias constants
     if (s.w2 > 32) return hipErrorInvalidValue;
-    return s.D == 128 ? launch_key<128, 1, false, 1>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st)
-                      : launch_key<64, 1, false, 1>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st);
+    return s.D == 128 ? launch_key<128, 1, false, 1>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st, ks, part)
+                      : launch_key<64, 1, false, 1>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st, ks, part);
   }
-  return bias ? mfma_bwd_key_b<true>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st)
-             : mfma_bwd_key_b<false>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, st);
+  return bias ? mfma_bwd_key_b<true>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, ks, part, st)
+             : mfma_bwd_key_b<false>(s, q, k, kp, v, vp, dout, lse, delta, dk, dv, ks, part, st);
 }
 
 }  // namespace sa

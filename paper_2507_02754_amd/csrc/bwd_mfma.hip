@@ -32,11 +32,23 @@ BwdPlan mfma_bwd_plan(const Shape& s) {
   p.G = s.w2 <= 32 ? 1 : 2;
   p.W2P = 32 * p.G;
   const long bh = static_cast<long>(s.B) * s.H;
-  // Chunk length: enough workgroups to fill the chip several times, at least
-  // one halo long, a multiple of every tile height.
+  // Chunk length, at least one halo long and a multiple of every tile height.
+  // One workgroup runs per CU, so a launch takes as long as its rounds of kCUs
+  // workgroups times a chunk's tiles (plus about half a tile to start one):
+  // shorter chunks than 128 where that is at least 5% less, i.e. where there
+  // are few of them (B=1 H=8 N=1021 w1=256: 64 chunks of 128 on 256 CUs took
+  // 444 us, 256 of 32 take 117), longer ones where there are more than 4096
+  // (fewer boundary sums).
+  constexpr long kCUs = 256;
+  const int QW = p.G == 1 ? 4 : 2;
+  auto rounds = [&](long n) { return static_cast<double>((n + kCUs - 1) / kCUs); };
+  auto cost = [&](long c) {
+    return rounds(bh * ((s.N + c - 1) / c)) * (static_cast<double>((c < s.N ? c : s.N) + QW - 1) / QW + 0.5);
+  };
   long cq = 128;
+  for (long c = cq / 2; c >= p.W2P && bh * ((s.N + 127) / 128) <= 2048; c /= 2)
+    if (cost(c) < 0.95 * cost(cq)) cq = c;
   while (cq < 1024 && bh * ((s.N + cq - 1) / cq) > 4096) cq *= 2;
-  if (cq < p.W2P) cq = p.W2P;
   const size_t halo_rows = static_cast<size_t>(p.W2P - 1);
   const size_t delta_bytes = ((bh * static_cast<size_t>(s.N) * 4) + 255) & ~size_t(255);
   auto set_chunk = [&](long c) {
@@ -58,6 +70,22 @@ BwdPlan mfma_bwd_plan(const Shape& s) {
     p.dqt_off = (p.bytes + 255) & ~size_t(255);
     p.bytes = p.dqt_off + bh * static_cast<size_t>(s.N) * 32 * s.D * 4;
   }
+  // Key side: the row blocks of a key block (128 keys, one workgroup per CU) go
+  // to ks workgroups where that shortens the rounds. In row blocks (about 1 us
+  // each): 5 to start and finish a workgroup, 8 where it stores float32 sums;
+  // their reduction is a launch (5 us) and reads the sums (4 MB in 1 us).
+  const long kb = static_cast<long>((s.N + 127) / 128) * s.B * s.Hkv;
+  const double rows = (127.0 + s.w1 < s.N ? 127.0 + s.w1 : s.N) * p.G * (s.H / s.Hkv);
+  const double sum_mb = 8e-6 * s.B * s.N * static_cast<double>(s.Hkv) * s.D;  // per split
+  auto key_cost = [&](int ks) {
+    return rounds(kb * ks) * (rows / ks + (ks > 1 ? 8 : 5)) + (ks > 1 ? 5 + ks * sum_mb / 4 : 0);
+  };
+  p.ks = 1;
+  p.key_off = (p.bytes + 255) & ~size_t(255);
+  const size_t key_bytes = 8 * static_cast<size_t>(s.B) * s.N * s.Hkv * s.D;  // per split
+  for (int ks = 2; ks <= 8; ++ks)
+    if ((s.ws_cap == 0 || p.key_off + ks * key_bytes <= s.ws_cap) && key_cost(ks) < 0.95 * key_cost(p.ks)) p.ks = ks;
+  if (p.ks > 1) p.bytes = p.key_off + p.ks * key_bytes;
   return p;
 }
 
@@ -724,7 +752,8 @@ hipError_t launch_stage(const Shape& s, BwdStage stage, const void* q, const voi
                          0, st, s, plan, halo, static_cast<uint16_t*>(g1), static_cast<uint16_t*>(g2));
     }
   } else {
-    return mfma_bwd_key(s, Q, K, KP, V, VP, DO, lse, delta, g0, g1, st);
+    return mfma_bwd_key(s, Q, K, KP, V, VP, DO, lse, delta, g0, g1, plan.ks,
+                        reinterpret_cast<float*>(wsb + plan.key_off), st);
   }
   return hipGetLastError();
 }

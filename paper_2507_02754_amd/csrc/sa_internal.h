@@ -91,9 +91,10 @@ hipError_t mfma_fwd(const Shape& s, const void* q, const void* k, const void* kp
 // partial sums (head/tail x dk'/dv', each [B*H, nchunks, W2P - 1, D] floats);
 // with determinant logits then the query side's dQ~ rows ([B*H, N, 32, D]
 // floats at dqt_off).
+// With ks > 1 (few key blocks) the key side's partial sums follow at key_off.
 struct BwdPlan {
-  int G, W2P, CQ, nchunks;
-  size_t halo_floats, delta_off, halo_off, dqt_off, bytes;
+  int G, W2P, CQ, nchunks, ks;
+  size_t halo_floats, delta_off, halo_off, dqt_off, key_off, bytes;
 };
 BwdPlan mfma_bwd_plan(const Shape& s);
 bool mfma_bwd_supported(const Shape& s);
@@ -105,10 +106,11 @@ hipError_t mfma_bwd_stage(const Shape& s, BwdStage stage, const void* q, const v
                           const float* lse, void* g0, void* g1, void* g2, void* workspace,
                           hipStream_t st);
 
-// Key-side backward stage of the MFMA path (dK, dV) given Delta.
+// Key-side backward stage of the MFMA path (dK, dV) given Delta; ks workgroups
+// per key block, their float32 sums in `part` ([ks, 2, B, N, Hkv, D], ks > 1).
 hipError_t mfma_bwd_key(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
                         const void* vp, const void* dout, const float* lse, const float* delta,
-                        void* dk, void* dv, hipStream_t st);
+                        void* dk, void* dv, int ks, float* part, hipStream_t st);
 
 // Fused backward (w2 <= 32, trilinear logits, bf16, head_dim 128, one K-side
 // head per query head): one kernel computes S and dP once per (row block, key
