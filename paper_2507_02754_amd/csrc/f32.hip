@@ -18,9 +18,12 @@
 //     add their float32 sums in a fixed order.
 //
 // Measured, forward + backward: float32, B=1 H=4 N=2000 D=64 w1=256 w2=16, 16.8 ms
-// on the plain kernels (one thread per pair, operands read per pair), 0.54 ms
-// here; bf16, N=1024 D=128 w1=w2=128, 44.8 ms and 2.9 ms. The matrix cores are
-// busy about half of the time at these sizes (one or two wavefronts per SIMD).
+// on the plain kernels (one thread per pair, operands read per pair), 0.50 ms
+// here; bf16, N=1024 D=128 w1=w2=128, 44.8 ms and 2.55 ms. The matrix cores are
+// busy 60% of the time at these sizes. Vector instructions are what costs the
+// rest: they add to the products' time even with two wavefronts per SIMD (6.9
+// per product: 0.54 ms; masks and operand checks on the edge blocks only: 0.50 ms), while loads issued further ahead of their use
+// changed nothing.
 //
 // Operand layout (lane = 32 h + c). A row operand (rows along the lanes): lane
 // (h, c) holds row c, columns 8 t + 4 h .. + 3 of float4 t; product 4 t + e
@@ -44,16 +47,21 @@ namespace {
 
 constexpr int kFWaves = 4;
 constexpr int kFThreads = 64 * kFWaves;
-constexpr int kRingMax = 132;  // k-rows of the query side's LDS ring (w2 <= 128)
+constexpr int kScratch = 32 * 33;  // floats of one wavefront's masked_tile scratch
 
 // log2(e) and ln 2 minus their float32 values
 constexpr float kLog2eLo = static_cast<float>(1.4426950408889634074 - static_cast<double>(kLog2e));
 constexpr float kLn2Lo = static_cast<float>(0.69314718055994530942 - static_cast<double>(kLn2));
-// 2^(x - lse log2 e): the normaliser's product is not rounded before the
-// difference (lse is several times larger than the differences that matter).
-__device__ __forceinline__ float prob(float x, float lse) {
-  return fast_exp2(__builtin_fmaf(-lse, kLog2eLo, __builtin_fmaf(-lse, kLog2e, x)));
-}
+// 2^(x - lse log2 e) with lse log2 e as hi + lo: the normaliser's product is not
+// rounded before the difference (it is several times larger than the differences
+// that matter). x has the scale in its q~, rounded as in the forward: its errors
+// then largely cancel against those in lse.
+struct Norm {
+  float hi, lo;
+  __device__ __forceinline__ explicit Norm(float lse)
+      : hi(lse * kLog2e), lo(__builtin_fmaf(lse, kLog2eLo, __builtin_fmaf(lse, kLog2e, -hi))) {}
+};
+__device__ __forceinline__ float prob(float x, const Norm& n) { return fast_exp2((x - n.hi) - n.lo); }
 
 __device__ __forceinline__ f32x16_t mfma_f32(float a, float b, f32x16_t c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
@@ -187,16 +195,18 @@ __device__ __forceinline__ void with_lw(int lw, F f) {
 
 __device__ __forceinline__ bool nonfinite(float x) { return !(fabsf(x) < __builtin_inff()); }
 
-template <typename T>
-__device__ __forceinline__ bool any_nonfinite(const TrChunk<T>& x) {
-  bool bad = false;
+// Whether a tile of products has an infinity or NaN: one in any operand row
+// reaches every lane of it (its masked pairs multiply it by 0), so the products
+// need no look at the operands. (Sums that overflow take the slow path too.)
+__device__ __forceinline__ bool any_nonfinite(const f32x16_t& u) {
+  float x = 0.f;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) bad |= nonfinite(to_f32(x.x[v]));
-  return __builtin_amdgcn_ballot_w64(bad) != 0;
+  for (int v = 0; v < 16; ++v) x += u[v];
+  return __builtin_amdgcn_ballot_w64(nonfinite(x)) != 0;
 }
 
 // One accumulator tile of sum over the 32 contraction rows x of p[x] op[x][d],
-// term by term and for the pairs with ok(x) only: the rare block whose operand
+// term by term and for the pairs with ok(x) only: the rare tile whose operand
 // holds infinities or NaN in rows that are masked for some lanes. p:
 // accumulator order; put through this wavefront's LDS scratch (32 x 33 floats)
 // so that the loop stays rolled. row(x, d, y) gives the operand's four values
@@ -241,7 +251,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
     const T* __restrict__ v, const T* __restrict__ vp, T* __restrict__ out, float* __restrict__ lse) {
   using Ge = Geo<D>;
   constexpr int NDT = Ge::NDT;
-  __shared__ float scratch[kFWaves][32 * 33];
+  __shared__ float scratch[kFWaves][kScratch];
   const int SP = 32 >> lw;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
@@ -312,11 +322,19 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
       // Online softmax over this block's 32 keys (16 in each lane half).
       float p[16], mx = -INFINITY;
 #pragma unroll
-      for (int vv = 0; vv < 16; ++vv) {
-        const int j = jb + acc_row(vv, h);
-        p[vv] = j >= lo && j <= i ? sc[vv] : -INFINITY;
-        mx = fmaxf(mx, p[vv]);
+      for (int vv = 0; vv < 16; ++vv) p[vv] = sc[vv];
+      // Blocks with keys that not every query of the wavefront sees.
+      const bool edge = jb < i0 + SP - w1 || jb + 31 > i0;
+      if (edge) {
+        asm volatile("" ::: "memory");  // a branch, not selects on every block
+#pragma unroll
+        for (int vv = 0; vv < 16; ++vv) {
+          const int j = jb + acc_row(vv, h);
+          p[vv] = j >= lo && j <= i ? p[vv] : -INFINITY;
+        }
       }
+#pragma unroll
+      for (int vv = 0; vv < 16; ++vv) mx = fmaxf(mx, p[vv]);
       const float mn = fmaxf(m, fmaxf(mx, swap_halves(mx)));
       const float mu = mn == -INFINITY ? 0.f : mn;  // no key of the row's window so far
       const float alpha = fast_exp2(m - mu);
@@ -327,9 +345,6 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
         p[vv] = fast_exp2(p[vv] - mu);
         l += p[vv];
       }
-      // Keys outside the union of the windows count as zero rows of V. Keys that
-      // only some of the wavefront's queries see: see masked_tile.
-      const bool split = SP > 1 && (jb < i0 + SP - w1 || jb + 31 > i0);
       bk = rows_from<T, D>(kb, jb + 32, N, rsb);  // the next block's
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) {
@@ -341,10 +356,10 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
         f32x16_t u = {};
 #pragma unroll
         for (int vv = 0; vv < 16; ++vv) {
-          const bool in = jb + acc_row(vv, h) <= jhi && (D >= 32 || c < D);
-          u = mfma_f32(in ? to_f32(cur.x[vv]) : 0.f, p[vv], u);
+          const float y = to_f32(cur.x[vv]);
+          u = mfma_f32(D >= 32 || c < D ? y : 0.f, p[vv], u);
         }
-        if (split && any_nonfinite(cur))
+        if (edge && any_nonfinite(u))
           u = masked_tile<D>(
               p, scratch[wave], c, h, [&](int x) { return jb + x >= lo && jb + x <= i; },
               [&](int x, int d, float* y) {
@@ -405,7 +420,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
 // chunk boundary are partial sums for the fix-up kernel. Where a head has too
 // few queries for chunks of W2T to fill the chip (plan.full) the chunks are
 // shorter than the k-row window, and every k-row leaves as a partial sum.
-template <typename T, int D>
+template <typename T, int D, bool BIAS>
 __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_kernel(
     Shape s, F32Plan plan, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ kp,
     const T* __restrict__ v, const T* __restrict__ vp, const T* __restrict__ dout,
@@ -414,8 +429,12 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
   using Ge = Geo<D>;
   constexpr int NDT = Ge::NDT, RS = D + 4;
   constexpr bool FLY = D >= 64;
-  __shared__ __attribute__((aligned(16))) float ring[2 * kRingMax * RS];
-  __shared__ __attribute__((aligned(16))) float dqx[kFWaves * 4 * D];
+  // Per wavefront kScratch floats (masked_tile's, or its dq rows at the end of a
+  // step), then the rings (as many rows as w2 asks for).
+  extern __shared__ __attribute__((aligned(16))) float f32_lds[];
+  static_assert(4 * D <= kScratch, "dq rows of a step");
+  float* const dqx = f32_lds;
+  float* const ring = f32_lds + kFWaves * kScratch;
   const int lw = plan.lw, SP = 32 >> lw, WT = plan.W2T;
   const int groups = plan.groups, QS = plan.qs, SQ = QS * SP;  // queries per step
   const int RB = WT + SQ;
@@ -441,9 +460,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
   const T* const vb = v + base;
   const int rsb = static_cast<int>(rs * sizeof(T));
   const int roff = c * rsb + 4 * h * static_cast<int>(sizeof(T)), toff = 4 * h * rsb + tr_col<T, D>(c);
-  // masked_tile scratch: only with several queries per step, where the ring is short
-  float* const scratch = ring + 48 * RS + wave * (32 * 33);
-  static_assert(48 * RS + kFWaves * 32 * 33 <= 2 * kRingMax * RS, "scratch behind the short rings");
+  float* const scratch = f32_lds + wave * kScratch;
 
   for (int x = tid; x < 2 * RB * RS; x += kFThreads) ring[x] = 0.f;
   __syncthreads();
@@ -497,7 +514,8 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
       aq[dt] = f32x16_t{};
     }
     if (busy && i0 < ce) {
-      const float lse_i = lse[stat + ic], dlt = delta[stat + ic];
+      const Norm norm(lse[stat + ic]);
+      const float dlt = delta[stat + ic];
       // q~ and do~ of the lane's row: in registers, or (FLY) formed again for
       // every block from rows that stay in L1 / L2.
       const __amdgpu_buffer_rsrc_t bq = rows_from<T, D>(q + base, i0, N, rsb), bg = rows_from<T, D>(dout + base, i0, N, rsb);
@@ -506,17 +524,20 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
       const int ro = (c >> lw) * rsb + 4 * h * static_cast<int>(sizeof(T));
       const int ko = rowvalid ? (kk - k0) * rsb + 4 * h * static_cast<int>(sizeof(T)) : kFar;
       float qt[FLY ? 1 : 4 * Ge::NF], ot[FLY ? 1 : 4 * Ge::NF];
-      auto form = [&](const RowChunk<T, D>& a, const RowChunk<T, D>& x, float f, float bias, float* y) {
+      // (a row outside the window or the sequence loads k', v' as zeros; its S
+      // and dP are masked below)
+      auto form = [&](const RowChunk<T, D>& a, const RowChunk<T, D>& x, bool scaled, float bias, float* y) {
 #pragma unroll
         for (int t = 0; t < Ge::RC; ++t)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[4 * t + e] = rowvalid ? a.x[t].at(e) * f * (x.x[t].at(e) + bias) : 0.f;
+          for (int e = 0; e < 4; ++e)
+            y[4 * t + e] = (scaled ? a.x[t].at(e) * qscale : a.x[t].at(e)) * plus_bias<BIAS>(x.x[t].at(e), bias);
       };
       if constexpr (!FLY) {
 #pragma unroll
         for (int ch = 0; ch < Ge::NRC; ++ch) {
-          form(load_rows<T, D>(bq, ro, ch), load_rows<T, D>(bkp, ko, ch), qscale, s.kp_bias, qt + 4 * Ge::RC * ch);
-          form(load_rows<T, D>(bg, ro, ch), load_rows<T, D>(bvp, ko, ch), 1.f, s.vp_bias, ot + 4 * Ge::RC * ch);
+          form(load_rows<T, D>(bq, ro, ch), load_rows<T, D>(bkp, ko, ch), true, s.kp_bias, qt + 4 * Ge::RC * ch);
+          form(load_rows<T, D>(bg, ro, ch), load_rows<T, D>(bvp, ko, ch), false, s.vp_bias, ot + 4 * Ge::RC * ch);
         }
       }
       __amdgpu_buffer_rsrc_t bk = rows_from<T, D>(kb, jlo, N, rsb);
@@ -536,7 +557,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
           for (int ch = 0; ch < Ge::NRC; ++ch) {
             float y[4 * Ge::RC];
             if constexpr (FLY) {
-              form(fa, fm, ph ? 1.f : qscale, ph ? s.vp_bias : s.kp_bias, y);
+              form(fa, fm, ph == 0, ph ? s.vp_bias : s.kp_bias, y);
             } else {
 #pragma unroll
               for (int e = 0; e < 4 * Ge::RC; ++e) y[e] = (ph ? ot : qt)[4 * Ge::RC * ch + e];
@@ -570,12 +591,12 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
         for (int vv = 0; vv < 16; ++vv) {
           const int j = jb + acc_row(vv, h);
           const bool ok = rowvalid && j >= lo && j <= i;
-          const float e = prob(sc[vv], lse_i);
+          const float e = prob(sc[vv], norm);
           p[vv] = ok ? e : 0.f;
           ds[vv] = ok ? e * (dp[vv] - dlt) : 0.f;
         }
         // Keys that only some of the step's queries see: see masked_tile.
-        const bool split = SP > 1 && (jb < i0 + SP - w1 || jb + 31 > i0);
+        const bool edge = jb < i0 + SP - w1 || jb + 31 > i0;  // keys that not every query sees
         // U~^T += V^T P^T, dQ~^T += K^T dS^T
         const __amdgpu_buffer_rsrc_t bkc = bk;  // this block's (bk moves on below)
 #pragma unroll
@@ -595,10 +616,10 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
           f32x16_t u = {};
 #pragma unroll
           for (int vv = 0; vv < 16; ++vv) {
-            const bool in = jb + acc_row(vv, h) <= jhi && (D >= 32 || c < D);
-            u = mfma_f32(in ? to_f32(cur.x[vv]) : 0.f, x < NDT ? p[vv] : ds[vv], u);
+            const float y = to_f32(cur.x[vv]);
+            u = mfma_f32(D >= 32 || c < D ? y : 0.f, x < NDT ? p[vv] : ds[vv], u);
           }
-          if (split && any_nonfinite(cur))
+          if (edge && any_nonfinite(u))
             u = masked_tile<D>(
                 x < NDT ? p : ds, scratch, c, h, [&](int y) { return rowvalid && jb + y >= lo && jb + y <= i; },
                 [&](int y, int d, float* z) {
@@ -618,7 +639,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
     // ---- end of the step: dq, then the k-row contributions ----
     if (busy) {
       const T* kr = kp + base + static_cast<size_t>(kc_) * rs;
-      float* dst = dqx + (wave * 4 + (c >> lw)) * D;
+      float* dst = dqx + wave * kScratch + (c >> lw) * D;
       with_lw(lw, [&](auto LC) __attribute__((always_inline)) {
         constexpr int LW = decltype(LC)::value;
 #pragma unroll
@@ -674,7 +695,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
       const int qi = x / D, d = x % D;
       if (ib + qi < ce) {
         float sum = 0.f;
-        for (int gg = 0; gg < groups; ++gg) sum += dqx[(((qi / SP) * groups + gg) * 4 + qi % SP) * D + d];
+        for (int gg = 0; gg < groups; ++gg) sum += dqx[((qi / SP) * groups + gg) * kScratch + (qi % SP) * D + d];
         st1(dq + base + static_cast<size_t>(ib + qi) * rs + d, sum * s.scale);
       }
     }
@@ -737,7 +758,7 @@ template <int D>
 constexpr int key_waves() {
   return D == 128 ? 4 : 8;  // head_dim 128 takes more than 256 registers
 }
-template <typename T, int D>
+template <typename T, int D, bool BIAS>
 __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
     Shape s, int lw, int ks, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ kp,
     const T* __restrict__ v, const T* __restrict__ vp, const T* __restrict__ dout,
@@ -746,7 +767,7 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
   using Ge = Geo<D>;
   constexpr int NDT = Ge::NDT, RS = D + 4, KW = key_waves<D>();
   // K and V operands, then masked_tile scratch; at the end the wavefronts' sums.
-  constexpr int kOps = 2 * 32 * D, kScr = KW * 32 * 33, kSum = KW * 32 * RS;
+  constexpr int kOps = 2 * 32 * D, kScr = KW * kScratch, kSum = KW * 32 * RS;
   __shared__ __attribute__((aligned(16))) float lds[kSum > kOps + kScr ? kSum : kOps + kScr];
   const int SP = 32 >> lw;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -827,7 +848,7 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
         const float4 w = opk[64 * (ch * Ge::RC + t)];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float x = okc ? a.x[t].at(e) * qscale * (m.x[t].at(e) + s.kp_bias) : 0.f;
+          const float x = a.x[t].at(e) * qscale * plus_bias<BIAS>(m.x[t].at(e), s.kp_bias);
           sc = mfma_f32(x, e == 0 ? w.x : e == 1 ? w.y : e == 2 ? w.z : w.w, sc);
         }
       }
@@ -871,7 +892,7 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
         const float4 w = opv[64 * (ch * Ge::RC + t)];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float x = okc ? a.x[t].at(e) * (m.x[t].at(e) + s.vp_bias) : 0.f;
+          const float x = a.x[t].at(e) * plus_bias<BIAS>(m.x[t].at(e), s.vp_bias);
           dp = mfma_f32(x, e == 0 ? w.x : e == 1 ? w.y : e == 2 ? w.z : w.w, dp);
         }
       }
@@ -883,18 +904,22 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
 #pragma unroll
     for (int vq = 0; vq < 4; ++vq) {
       const int i = i0 + ((8 * vq) >> lw);  // eight rows share a query
-      const float lse_i = lse[stat + min(i, N - 1)], dlt = delta[stat + min(i, N - 1)];
+      const Norm norm(lse[stat + min(i, N - 1)]);
+      const float dlt = delta[stat + min(i, N - 1)];
       const bool okj = j <= i && j > i - w1 && j < N;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int vv = 4 * vq + e;
         const bool ok = okj && okr(vv);
-        const float x = prob(sc[vv], lse_i);
+        const float x = prob(sc[vv], norm);
         p[vv] = ok ? x : 0.f;
         ds[vv] = ok ? x * (dp[vv] - dlt) : 0.f;
       }
     }
-    const bool split = i0 < j0 + 31 || i0 + SP - 1 - w1 >= j0;  // rows that only some of the 32 keys see
+    // Row blocks with rows that not all of the 32 keys see, or (w2 not filling
+    // them, the start of the sequence) that are no pair's.
+    const bool edge = i0 < j0 + 31 || i0 + SP - 1 - w1 >= j0 || j0 + 32 > N || room[0] < 8 || room[1] < 8 ||
+                      room[2] < 8 || room[3] < 8;
     auto seen = [&](int r) {
       const int i = i0 + (r >> lw);
       return tof(r) < lim(r >> lw) && j <= i && j > i - w1 && j < N;
@@ -911,21 +936,18 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
       }
       const float bias = x < NDT ? s.vp_bias : s.kp_bias;
       f32x16_t u = {};
-      bool bad = false;
 #pragma unroll
       for (int vv = 0; vv < 16; ++vv) {
-        const float y = to_f32(ca[vv >> 2]) * (to_f32(cm.x[vv]) + bias);
-        const float z = okr(vv) && (D >= 32 || c < D) ? y : 0.f;
-        bad |= nonfinite(z);
-        u = mfma_f32(z, x < NDT ? p[vv] : ds[vv], u);
+        const float y = to_f32(ca[vv >> 2]) * plus_bias<BIAS>(to_f32(cm.x[vv]), bias);
+        u = mfma_f32(D >= 32 || c < D ? y : 0.f, x < NDT ? p[vv] : ds[vv], u);
       }
-      if (split && __builtin_amdgcn_ballot_w64(bad) != 0)
-        u = masked_tile<D>(x < NDT ? p : ds, lds + kOps + wave * (32 * 33), c, h, seen, [&](int r, int d, float* z) {
+      if (edge && any_nonfinite(u))
+        u = masked_tile<D>(x < NDT ? p : ds, lds + kOps + wave * kScratch, c, h, seen, [&](int r, int d, float* z) {
           const int at = (32 * dt + d) * static_cast<int>(sizeof(T));
           const Raw4<T> y0 = ldb4<T>(x < NDT ? bg : bq, (r >> lw) * rsb + at);
           const Raw4<T> y1 = ldb4<T>(x < NDT ? bvp : bkp, (i0 - k0 + (r >> lw) - tof(r)) * rsb + at);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) z[e] = y0.at(e) * (y1.at(e) + bias);
+          for (int e = 0; e < 4; ++e) z[e] = y0.at(e) * plus_bias<BIAS>(y1.at(e), bias);
         });
       if (x < NDT)
         av[dt] += u;
@@ -999,12 +1021,15 @@ hipError_t bwd_go(const Shape& s, BwdStage stage, const void* q_, const void* k_
   const auto *q = static_cast<const T*>(q_), *k = static_cast<const T*>(k_), *kp = static_cast<const T*>(kp_);
   const auto *v = static_cast<const T*>(v_), *vp = static_cast<const T*>(vp_), *dout = static_cast<const T*>(dout_);
   const F32Plan plan = f32_bwd_plan(s);
+  const bool bias = s.kp_bias != 0.f || s.vp_bias != 0.f;
   if (stage == BwdStage::Key) {
     const long total = static_cast<long>((s.N + 31) / 32) * plan.ks * s.B * s.H;
     float* part = halo + plan.key_floats;
-    hipLaunchKernelGGL((bwd_key_f32_kernel<T, D>), dim3(xcd_grid(total)), dim3(64 * key_waves<D>()), 0, st, s,
-                       row_bits(s.w2), plan.ks, q, k, kp, v, vp, dout, lse, delta, static_cast<T*>(g0),
-                       static_cast<T*>(g1), part);
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(64 * key_waves<D>()), 0, st, s, row_bits(s.w2), plan.ks, q, k,
+                         kp, v, vp, dout, lse, delta, static_cast<T*>(g0), static_cast<T*>(g1), part);
+    };
+    bias ? go(bwd_key_f32_kernel<T, D, true>) : go(bwd_key_f32_kernel<T, D, false>);
     if (plan.ks > 1) {
       const size_t n = static_cast<size_t>(s.B) * s.H * s.N * D;
       hipLaunchKernelGGL(key_sum_f32_kernel<T>, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, st, s,
@@ -1013,8 +1038,12 @@ hipError_t bwd_go(const Shape& s, BwdStage stage, const void* q_, const void* k_
     return hipGetLastError();
   }
   const long total = static_cast<long>(plan.nchunks) * s.B * s.H;
-  hipLaunchKernelGGL((bwd_query_f32_kernel<T, D>), dim3(xcd_grid(total)), dim3(kFThreads), 0, st, s, plan, q, k, kp, v,
-                     vp, dout, lse, delta, static_cast<T*>(g0), static_cast<T*>(g1), static_cast<T*>(g2), halo);
+  const size_t lds = 4 * (kFWaves * kScratch + 2 * (plan.W2T + plan.qs * (32 >> plan.lw)) * (D + 4));
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(kFThreads), lds, st, s, plan, q, k, kp, v, vp, dout, lse, delta,
+                       static_cast<T*>(g0), static_cast<T*>(g1), static_cast<T*>(g2), halo);
+  };
+  bias ? go(bwd_query_f32_kernel<T, D, true>) : go(bwd_query_f32_kernel<T, D, false>);
   if (plan.nchunks > 1) {
     const long n = static_cast<long>(s.B) * s.H * D *
                    (plan.full ? s.N : static_cast<long>(plan.nchunks - 1) * (plan.W2T - 1));
