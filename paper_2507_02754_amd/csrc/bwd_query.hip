@@ -344,7 +344,7 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
               fk[2 + 2 * e] = bf16_lo(ka[e]), fk[3 + 2 * e] = bf16_hi(ka[e]);
               fq[2 + 2 * e] = bf16_lo(qa[e]), fq[3 + 2 * e] = bf16_hi(qa[e]);
             }
-            cross8_rt<3 * (D / 3)>(fk, fq, ch, cr);
+            cross8_t<3 * (D / 3)>(fk, fq, t, h, cr);
             if (rowvalid) {
 #pragma unroll
               for (int e = 0; e < 4; ++e) a4[e] = pack_bf16x2(cr[2 * e] * qscale, cr[2 * e + 1] * qscale);

@@ -386,22 +386,10 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_mfma_kernel(Shape s, const ui
           fk[3 + 2 * w] = plus_bias<BIAS>(bf16_hi(kc[w]), kb);
           fq[2 + 2 * w] = bf16_lo(qc[w]), fq[3 + 2 * w] = bf16_hi(qc[w]);
         }
-        // component e of the fragment sits at position m of its chunk, which
-        // starts at window index e + 2 - m; m = (8 ch + e) mod 3 = (t + 2h + e) mod 3.
-        auto cross = [&](int e, int m) __attribute__((always_inline)) {
-          const int b = e + 2 - m;
-          return m == 0 ? fk[b + 1] * fq[b + 2] - fk[b + 2] * fq[b + 1]
-               : m == 1 ? fk[b + 2] * fq[b] - fk[b] * fq[b + 2]
-                        : fk[b] * fq[b + 1] - fk[b + 1] * fq[b];
-        };
         float cr[8];
+        cross8_t<DC>(fk, fq, t, h, cr);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float x = h == 0 ? cross(e, (t + e) % 3) : cross(e, (t + 2 + e) % 3);
-          cr[e] = 8 * ch + e < DC ? x * qscale : 0.f;
-        }
-#pragma unroll
-        for (int w = 0; w < 4; ++w) qt[t][w] = keep & pack_bf16x2(cr[2 * w], cr[2 * w + 1]);
+        for (int w = 0; w < 4; ++w) qt[t][w] = keep & pack_bf16x2(cr[2 * w] * qscale, cr[2 * w + 1] * qscale);
       }
     }
   } else {

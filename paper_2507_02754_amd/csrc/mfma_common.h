@@ -117,6 +117,24 @@ __device__ __forceinline__ void cross8_rt(const float* x, const float* y, int ch
     out[e] = 8 * ch + e < DC ? v : 0.f;
   }
 }
+// The same where ch = 2 t + h with t known at compile time (an unrolled loop)
+// and h the lane half: the position is (t + 2 h + e) mod 3, so two forms and one
+// select on h are enough. (Indexing the windows with e + 2 - m instead left them
+// in scratch memory.)
+template <int DC>
+__device__ __forceinline__ void cross8_t(const float* x, const float* y, int t, int h, float* out) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float c0 = x[e + 3] * y[e + 4] - x[e + 4] * y[e + 3];  // m = 0
+    const float c1 = x[e + 3] * y[e + 1] - x[e + 1] * y[e + 3];  // m = 1
+    const float c2 = x[e] * y[e + 1] - x[e + 1] * y[e];          // m = 2
+    const int m0 = (t + e) % 3, m1 = (t + 2 + e) % 3;
+    float v0 = m0 == 0 ? c0 : m0 == 1 ? c1 : c2, v1 = m1 == 0 ? c0 : m1 == 1 ? c1 : c2;
+    if (16 * t + e >= DC) v0 = 0.f;
+    if (16 * t + 8 + e >= DC) v1 = 0.f;
+    out[e] = h == 0 ? v0 : v1;
+  }
+}
 // Byte-range of one head's rows of a [.., N, H, D] bf16 tensor, from row 0 to
 // the end of row N-1 (rows are rs_bytes apart).
 __device__ __forceinline__ unsigned head_bytes(int N, int rs_bytes, int D) {
