@@ -144,6 +144,20 @@ def simplicial_attn_bwd_gqa_workspace_size(B, N, H, Hkv, D, w1, w2, dtype):
 
 
 def _check_inputs(tensors, names):
+    """(shape, dtype code) of tensors that all are contiguous [B, N, H, D] of one
+    shape, dtype and GPU; raises for the first that is not."""
+    t0 = tensors[0]
+    shape, dtype, device = t0.shape, t0.dtype, t0.device
+    if len(shape) == 4 and dtype in _DTYPES and device.type == "cuda":
+        for t in tensors:
+            if not (t.is_contiguous() and t.dtype is dtype and t.shape == shape and t.device == device):
+                break
+        else:
+            return shape, _DTYPES[dtype]
+    _refuse_inputs(tensors, names)
+
+
+def _refuse_inputs(tensors, names):
     t0 = tensors[0]
     if t0.dim() != 4:
         raise ValueError(f"{names[0]} must be [B, N, H, D], got shape {tuple(t0.shape)}")
@@ -160,15 +174,16 @@ def _check_inputs(tensors, names):
             raise ValueError(f"{n} has shape {tuple(t.shape)}, expected {tuple(t0.shape)}")
         if not t.is_contiguous():
             raise ValueError(f"{n} must be contiguous [B, N, H, D]")
-    return t0.shape, _DTYPES[t0.dtype]
 
 
+# Pointers and streams go to the library as plain integers (the declared argument
+# types convert them).
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def simplicial_attn_fwd(q, k, kp, v, vp, w1, w2, scale=None, out=None, lse=None):
@@ -202,14 +217,15 @@ def _fwd(entry, q, k, kp, v, vp, w1, w2, scale, out, lse, biases=()):
         out = torch.empty_like(q)
     else:
         _check_inputs((q, out), ("q", "out"))
+    device = q.device
     if lse is None:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
+        lse = torch.empty((B, H, N), dtype=torch.float32, device=device)
     elif lse.shape != (B, H, N) or lse.dtype != torch.float32 or not lse.is_contiguous() \
-            or lse.device != q.device:
+            or lse.device != device:
         raise ValueError("lse must be a contiguous float32 [B, H, N] tensor on the inputs' device")
-    rc = getattr(load_library(), entry)(
-        _ptr(q), _ptr(k), _ptr(kp), _ptr(v), _ptr(vp), _ptr(out), _ptr(lse),
-        B, N, H, D, int(w1), int(w2), float(scale), *biases, dt, _stream(q.device))
+    rc = getattr(_lib or load_library(), entry)(
+        q.data_ptr(), k.data_ptr(), kp.data_ptr(), v.data_ptr(), vp.data_ptr(), out.data_ptr(), lse.data_ptr(),
+        B, N, H, D, int(w1), int(w2), float(scale), *biases, dt, _stream(device))
     if rc != 0:
         raise SimplicialAttnError(rc, entry)
     return out, lse
@@ -266,7 +282,7 @@ def simplicial_attn_bwd_preprocess(out, dout, w1, w2, workspace):
     """Delta_i = <dO_i, O_i> into `workspace` (a uint8 GPU tensor of the backward's size)."""
     (B, N, H, D), dt = _check_inputs((out, dout), ("out", "dout"))
     rc = load_library().simplicial_attn_bwd_preprocess(
-        _ptr(out), _ptr(dout), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
+        _ptr(out), _ptr(dout), _ptr(workspace), workspace.numel(),
         B, N, H, D, int(w1), int(w2), dt, _stream(out.device))
     if rc != 0:
         raise SimplicialAttnError(rc, "simplicial_attn_bwd_preprocess")
@@ -282,7 +298,7 @@ def simplicial_attn_bwd_query_side(q, k, kp, v, vp, dout, lse, w1, w2, workspace
     _check_inputs((q, *grads), ("q", "dq", "dkp", "dvp"))
     rc = load_library().simplicial_attn_bwd_query_side(
         _ptr(q), _ptr(k), _ptr(kp), _ptr(v), _ptr(vp), _ptr(dout), _ptr(lse),
-        *(_ptr(g) for g in grads), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
+        *(_ptr(g) for g in grads), _ptr(workspace), workspace.numel(),
         B, N, H, D, int(w1), int(w2), float(scale), dt, _stream(q.device))
     if rc != 0:
         raise SimplicialAttnError(rc, "simplicial_attn_bwd_query_side")
@@ -298,7 +314,7 @@ def simplicial_attn_bwd_key_side(q, k, kp, v, vp, dout, lse, w1, w2, workspace, 
     _check_inputs((q, *grads), ("q", "dk", "dv"))
     rc = load_library().simplicial_attn_bwd_key_side(
         _ptr(q), _ptr(k), _ptr(kp), _ptr(v), _ptr(vp), _ptr(dout), _ptr(lse),
-        *(_ptr(g) for g in grads), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
+        *(_ptr(g) for g in grads), _ptr(workspace), workspace.numel(),
         B, N, H, D, int(w1), int(w2), float(scale), dt, _stream(q.device))
     if rc != 0:
         raise SimplicialAttnError(rc, "simplicial_attn_bwd_key_side")
@@ -322,7 +338,7 @@ def simplicial_attn_bwd_fused(q, k, kp, v, vp, dout, lse, w1, w2, workspace, sca
     _check_inputs((q, *grads), ("q", "dk", "dv"))
     rc = load_library().simplicial_attn_bwd_fused(
         _ptr(q), _ptr(k), _ptr(kp), _ptr(v), _ptr(vp), _ptr(dout), _ptr(lse),
-        *(_ptr(g) for g in grads), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
+        *(_ptr(g) for g in grads), _ptr(workspace), workspace.numel(),
         B, N, H, D, int(w1), int(w2), float(scale), float(kp_bias), float(vp_bias), dt, _stream(q.device))
     if rc != 0:
         raise SimplicialAttnError(rc, "simplicial_attn_bwd_fused")
@@ -337,7 +353,7 @@ def simplicial_attn_bwd_fused_reduce(q, w1, w2, workspace, scale=None, grads=Non
     grads = grads if grads is not None else tuple(torch.empty_like(q) for _ in range(3))
     _check_inputs((q, *grads), ("q", "dq", "dkp", "dvp"))
     rc = load_library().simplicial_attn_bwd_fused_reduce(
-        *(_ptr(g) for g in grads), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
+        *(_ptr(g) for g in grads), _ptr(workspace), workspace.numel(),
         B, N, H, D, int(w1), int(w2), float(scale), dt, _stream(q.device))
     if rc != 0:
         raise SimplicialAttnError(rc, "simplicial_attn_bwd_fused_reduce")
@@ -410,9 +426,9 @@ def _bwd(entry, q, k, kp, v, vp, out, dout, lse, w1, w2, scale, grads, workspace
     else:
         _check_inputs((q, *grads), ("q", "dq", "dk", "dkp", "dv", "dvp"))
     workspace = _workspace(workspace, B, N, H, D, w1, w2, dt, q.device)
-    rc = getattr(load_library(), entry)(
+    rc = getattr(_lib or load_library(), entry)(
         _ptr(q), _ptr(k), _ptr(kp), _ptr(v), _ptr(vp), _ptr(out), _ptr(dout), _ptr(lse),
-        *(_ptr(g) for g in grads), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
+        *(_ptr(g) for g in grads), _ptr(workspace), workspace.numel(),
         B, N, H, D, int(w1), int(w2), float(scale), *biases, dt, _stream(q.device))
     if rc != 0:
         raise SimplicialAttnError(rc, entry)
@@ -443,7 +459,7 @@ def simplicial_attn_bwd_gqa(q, k, kp, v, vp, out, dout, lse, w1, w2, scale=None,
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
     rc = load_library().simplicial_attn_bwd_gqa(
         _ptr(q), _ptr(k), _ptr(kp), _ptr(v), _ptr(vp), _ptr(out), _ptr(dout), _ptr(lse),
-        *(_ptr(g) for g in grads), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
+        *(_ptr(g) for g in grads), _ptr(workspace), workspace.numel(),
         B, N, H, Hkv, D, int(w1), int(w2), float(scale), dt, _stream(q.device))
     if rc != 0:
         raise SimplicialAttnError(rc, "simplicial_attn_bwd_gqa")
