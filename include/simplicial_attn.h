@@ -183,10 +183,9 @@ int simplicial_attn_bwd_noalloc(const void* q, const void* k, const void* kp, co
  * (logits) carries no scale factor: scale = 1 is the paper's form.
  * Kernels: for bf16 data with D in {64, 128} and w2 <= 32 both run on the MFMA
  * kernels (the modulated query of the trilinear kernels is formed as the
- * chunkwise cross product k'_k x q_i; the backward's workspace then also
- * holds the query side's fp32 dQ~ rows, 4 * 32 * D bytes per query and head,
- * from which a separate kernel forms dQ and dK'); every other shape runs on
- * the plain fp32 kernels.
+ * chunkwise cross product k'_k x q_i, and dQ and dK' as cross products of the
+ * query side's sums with k'_k and q_i); every other shape runs on the plain
+ * fp32 kernels.
  */
 int simplicial_attn_det_fwd(const void* q, const void* k, const void* kp, const void* v,
                             const void* vp, void* out, float* lse, int64_t B, int64_t N, int64_t H,

@@ -84,8 +84,7 @@ size_t workspace_bytes_for(int64_t B, int64_t N, int64_t H, int64_t D, int32_t w
   return sa::f32_bwd_plan(s).bytes;
 }
 
-// Backward workspace of the determinant logits: the MFMA plan (with the dQ~
-// rows) where the MFMA kernels take the shape, else Delta only.
+// Backward workspace of the determinant logits: the MFMA plan where the MFMA kernels take the shape, else Delta only.
 size_t det_workspace_bytes_for(int64_t B, int64_t N, int64_t H, int64_t D, int32_t w1, int32_t w2,
                                int32_t dtype) {
   if (check_sizes(B, N, H, D, w1, w2, dtype) != SA_OK) return 0;

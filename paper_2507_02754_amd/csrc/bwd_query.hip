@@ -60,20 +60,48 @@ struct QueryLds {
   static constexpr int bytes = qringOff + 2 * RQ * 2 * D;
 };
 
+// Columns of role B's dQ~ accumulators under determinant logits, where dq_i =
+// scale sum_k dQ~_r x k'_k and dk'_k = scale sum_i q_i x dQ~_r take cross
+// products within 3-component chunks. In the accumulator layout a chunk's
+// components lie in both lane halves; but the rows of dQ~^T are the columns of
+// K, and the transposing read can fetch them in any order of groups of four. So
+// group g of half h (registers 4 g .. 4 g + 3) is given column group col(g, h):
+// first units of three groups (four whole chunks), the same positions in both
+// halves, so that the cross products are register arithmetic without selects;
+// last LO groups per half that no unit takes (their chunks may straddle the
+// halves: exchanged). D = 128 pairs units 4 apart (12 groups = 4 mod 8 bank
+// groups): the transposing reads then have no bank conflicts.
+template <int D>
+struct DetCols {
+  static constexpr int NG = D / 8;              // groups per half
+  static constexpr int LO = D == 128 ? 1 : 2;   // groups of a half in no unit
+  static constexpr int C0 = D - 8 * LO;         // first column of those
+  static constexpr int M = D == 128 ? 12 : 6;   // leading groups of each half, M apart
+  static_assert((NG - LO) % 3 == 0 && C0 % 3 == 0, "whole chunks");
+  __device__ static __forceinline__ int col(int g, int h) {
+    if (g < M) return g + M * h;
+    if (g < NG - LO) return 2 * M + (g - M) + (NG - LO - M) * h;
+    return C0 / 4 + (g - (NG - LO)) + LO * h;
+  }
+};
+
 // FORM 1: determinant logits (Section 5): role A forms q~ = (scale log2 e)
-// k'_k x q_i per 3-component chunk; role B stores its dQ~ rows (fp32, [B*H,
-// N, 32, D]) in dqt instead of reducing them, because dq_i = scale sum_k
-// dQ~_r x k'_k and dk'_k = scale sum_i q_i x dQ~_r mix components of a chunk
-// that lie in different lane halves; a separate kernel forms them.
+// k'_k x q_i per 3-component chunk, and role B reads K's columns in the order
+// of DetCols, so that its epilogue forms dq and the dk' contributions in
+// registers as the trilinear form does: 1.61 ms at B=1, H=16, N=4096, D=128,
+// w1=512, w2=32, against 1.59 ms where it stored its fp32 dQ~ rows (16 KiB per
+// query and head) plus 0.51 ms for the two kernels that formed dq and dk' from
+// them at the rate of memory.
 template <int D, bool BIAS, int FORM>
 __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
     Shape s, BwdPlan plan, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ kp, const uint16_t* __restrict__ v, const uint16_t* __restrict__ vp,
     const uint16_t* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
     uint16_t* __restrict__ dq, uint16_t* __restrict__ dkp, uint16_t* __restrict__ dvp,
-    float* __restrict__ ws, float* __restrict__ dqt) {
+    float* __restrict__ ws) {
   constexpr int NT = D / 16, NDT = D / 32;
   using L = QueryLds<D>;
+  using DC = DetCols<D>;
   using T = typename L::T;  // layout of the k'/v' row ring
   constexpr int QW = L::QW, W2P = L::W2P, RB = L::RB, RK = L::RK, RQ = L::RQ, RL = L::RL, NS = L::NS;
   constexpr int SW = D / QW;  // columns of one ring phase slice
@@ -256,9 +284,11 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
   // contributions in a fixed order.
   // hook(IC<p>) runs in phase p before its barrier (register-only work that
   // fills the wait).
-  auto ring_add = [&](float* ring, f32x16_t* x, bool rowvalid, int kk, auto hook) __attribute__((always_inline)) {
+  // Registers 4 g .. 4 g + 3 of x are columns col(g) .. col(g) + 3; a slice is
+  // a quarter of the g.
+  auto ring_add = [&](float* ring, f32x16_t* x, bool rowvalid, int kk, auto col, auto hook) __attribute__((always_inline)) {
     const int aslot = (kk - kbase) % RB;
-    float* rp = ring + aslot * L::rStride + 4 * h;
+    float* rp = ring + aslot * L::rStride;
     auto phase = [&](auto PC) __attribute__((always_inline)) {
       constexpr int p = decltype(PC)::value;
       const int sl = (qs + p) % QW;
@@ -272,7 +302,7 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
           for (int qd = 0; qd < 4; ++qd) {
             const int d0 = 32 * dt + 8 * qd;
             if (d0 / SW != slc) continue;
-            xa[4 * dt + qd] = *reinterpret_cast<const float4*>(rp + d0);
+            xa[4 * dt + qd] = *reinterpret_cast<const float4*>(rp + col(4 * dt + qd));
           }
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
@@ -285,7 +315,7 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
             y.y += x[dt][4 * qd + 1];
             y.z += x[dt][4 * qd + 2];
             y.w += x[dt][4 * qd + 3];
-            *reinterpret_cast<float4*>(rp + d0) = y;
+            *reinterpret_cast<float4*>(rp + col(4 * dt + qd)) = y;
           }
       }
       hook(PC);
@@ -439,7 +469,7 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
           }
       }
       lds_barrier();  // matches B's barrier after its dq reduction
-      ring_add(ring_vp, au, rowvalid, kk, [](auto) {});
+      ring_add(ring_vp, au, rowvalid, kk, [&](int g) { return 8 * g + 4 * h; }, [](auto) {});
       // No barrier after the flush: the rows it reads and clears are next
       // written by the ring phases of the next tile, past its barriers.
       flush_tile(i0);
@@ -448,6 +478,36 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
     u32x4_t ot[NT];
     f32x16_t adq[NDT];
     int it = 0;
+    // Transposing reads of K in the column order of DetCols: lane s of a
+    // 16-lane group addresses the four columns of group 2 p + s / 2 % 2 of half
+    // s % 2 (p: the group's parity), from accumulator tile 0 on and, for the
+    // last tile, where the order is another.
+    int dbase[2][2];
+    if constexpr (FORM == 1) {
+      const int grp = lane >> 4, sl = lane & 15, qd = 2 * (grp & 1) + ((sl >> 1) & 1);
+#pragma unroll
+      for (int last = 0; last < 2; ++last) {
+        const int cg = DC::col((last ? DC::NG - 4 : 0) + qd, sl & 1);
+        const int t = cg >> 2, hd = (cg >> 1) & 1;
+#pragma unroll
+        for (int second = 0; second < 2; ++second)
+          dbase[last][second] = 1024 * t + 512 * hd + (4 * ((grp >> 1) ^ hd) + (sl >> 2)) * 16 + 8 * (cg & 1) +
+                                128 * (second ^ (t & 1));
+      }
+    }
+    auto frag_k = [&](int off, int dt, int uu) {
+      if constexpr (FORM == 1) {
+        const int o = off + 256 * uu + (dt == NDT - 1 ? 0 : 1024 * dt);
+        const int last = dt == NDT - 1, odd = last ? 0 : dt & 1;
+        const u32x2_t a = lds_tr16(lds + dbase[last][odd] + o);
+        const u32x2_t bb = lds_tr16(lds + dbase[last][odd ^ 1] + o);
+        return u32x4_t{a[0], a[1], bb[0], bb[1]};
+      } else {
+        return frag_tr(off, dt, uu);
+      }
+    };
+    // Column of register 4 g of adq.
+    auto col = [&](int g) { return FORM == 1 ? 4 * DC::col(g, h) : 8 * g + 4 * h; };
     for (int tile = 0; tile < ntiles; ++tile) {
       const int i0 = cs + tile * QW;
       const int i = i0 + qs;
@@ -500,7 +560,7 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
 #pragma unroll
         for (int uu = 0; uu < 2; ++uu)
 #pragma unroll
-          for (int dt = 0; dt < NDT; ++dt) ktr[uu][dt] = frag_tr(so, dt, uu);
+          for (int dt = 0; dt < NDT; ++dt) ktr[uu][dt] = frag_k(so, dt, uu);
         if constexpr (decltype(next)::value) dout_ = dprod((it_ + 1) % NS);
 #pragma unroll
         for (int uu = 0; uu < 2; ++uu) {
@@ -536,30 +596,83 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
       }
       // ---- tile epilogue (B): dq_i, then scale q_i o dQ~_r into the dk' ring ----
       if (rowloader && tile + 1 < ntiles) row_put(i0 + QW, nrow);
-      if constexpr (FORM == 1) {
-        // dQ~ rows to dqt (row c of query i, d = 32 dt + 8 qd + 4 h + e);
-        // the ring phases keep their barriers (matching role A) without adds.
-        if (qvalid) {
-          float* dst = dqt + ((static_cast<size_t>(bh) * N + i) * 32 + c) * D;
-#pragma unroll
-          for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd)
-              *reinterpret_cast<float4*>(dst + 32 * dt + 8 * qd + 4 * h) =
-                  float4{adq[dt][4 * qd], adq[dt][4 * qd + 1], adq[dt][4 * qd + 2], adq[dt][4 * qd + 3]};
-        }
-        lds_barrier();  // matches the barrier before role A's ring phases
-        ring_add(ring_kp, adq, false, kk, [](auto) {});
-        flush_tile(i0);
-        continue;
-      }
       // dq_i = scale * sum_k k'_k o dQ~_(i,k): every lane multiplies its
       // accumulators (row c, d = 32 dt + 8 (v/4) + 4 h + v%4) by k'_k, then
       // the sums over the 32 rows run across lanes in registers: the first
       // level here, the other four in the ring phases below (their waits).
       constexpr int NV = 16 * NDT;
       float xv[NV];
-      {
+      if constexpr (FORM == 1) {
+        // The same with cross products: xv = dQ~_r x k'_k, dQ~_r = scale q_i x
+        // dQ~_r. Rows that are no pair's count as zeros times the query's own
+        // k' row (what lies in their own slot may not be finite).
+        if (!rowvalid) {
+#pragma unroll
+          for (int dt = 0; dt < NDT; ++dt) adq[dt] = f32x16_t{};
+        }
+        const int rslot = rowvalid ? kslot : (i - kbase) % RK;
+        const char* kr = kring + rslot * 2 * D;
+        const char* qr = qring + ((i - cs) % RQ) * 2 * D;  // q_i
+        const int sw = T::swz(rslot);
+        auto quad = [&](const char* at, float* y) {
+          const u32x2_t m = *reinterpret_cast<const u32x2_t*>(at);
+          y[0] = bf16_lo(m[0]), y[1] = bf16_hi(m[0]), y[2] = bf16_lo(m[1]), y[3] = bf16_hi(m[1]);
+        };
+        auto kquad = [&](int cg, float* y) { quad(kr + 16 * ((cg >> 1) ^ sw) + 8 * (cg & 1), y); };
+        // n components from chunk boundaries on: dq part and dk' part
+        auto crosses = [&](const float* a, const float* kf, const float* qf, auto n, float* gq, float* gk) __attribute__((always_inline)) {
+#pragma unroll
+          for (int x = 0; x < decltype(n)::value; ++x) {
+            const int c0 = x - x % 3, u = c0 + (x + 1) % 3, w = c0 + (x + 2) % 3;
+            gq[x] = a[u] * kf[w] - a[w] * kf[u];
+            gk[x] = s.scale * (qf[u] * a[w] - qf[w] * a[u]);
+          }
+        };
+#pragma unroll
+        for (int g = 0; g < DC::NG - DC::LO; g += 3) {
+          float a[12], kf[12], qf[12], gq[12], gk[12];
+#pragma unroll
+          for (int y = 0; y < 3; ++y) {
+            const int cg = DC::col(g + y, h);
+            kquad(cg, kf + 4 * y);
+            quad(qr + 8 * cg, qf + 4 * y);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[4 * y + e] = adq[(g + y) / 4][4 * ((g + y) % 4) + e];
+          }
+          crosses(a, kf, qf, std::integral_constant<int, 12>(), gq, gk);
+#pragma unroll
+          for (int y = 0; y < 12; ++y) {
+            xv[4 * g + y] = gq[y];
+            adq[(4 * g + y) / 16][(4 * g + y) % 16] = gk[y];
+          }
+          __builtin_amdgcn_sched_barrier(0);  // no more k' and q values in registers at once
+        }
+        // Columns C0 .. D - 1, of both halves in each.
+        constexpr int NL = 8 * DC::LO, R0 = NV - NL / 2;
+        float a[NL], kf[NL], qf[NL], gq[NL], gk[NL];
+#pragma unroll
+        for (int x = 0; x < NL / 2; ++x) {
+          const unsigned y = __float_as_uint(adq[(R0 + x) / 16][(R0 + x) % 16]);
+          const auto p = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+          a[x] = __uint_as_float(p[0]);
+          a[NL / 2 + x] = __uint_as_float(p[1]);
+        }
+#pragma unroll
+        for (int y = 0; y < NL / 4; ++y) {
+          kquad(DC::C0 / 4 + y, kf + 4 * y);
+          quad(qr + 2 * DC::C0 + 8 * y, qf + 4 * y);
+        }
+        crosses(a, kf, qf, std::integral_constant<int, NL - NL % 3>(), gq, gk);
+#pragma unroll
+        for (int x = NL - NL % 3; x < NL; ++x) gq[x] = gk[x] = 0.f;  // in no logit
+#pragma unroll
+        for (int x = 0; x < NL / 2; ++x) {
+          const float q0 = gq[x], q1 = gq[NL / 2 + x], k0 = gk[x], k1 = gk[NL / 2 + x];
+          xv[R0 + x] = h == 0 ? q0 : q1;
+          adq[(R0 + x) / 16][(R0 + x) % 16] = h == 0 ? k0 : k1;
+        }
+        reduce_lanes32_level<NV, 0>(xv, lane);
+      } else {
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
@@ -586,15 +699,14 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
           }
       }
       lds_barrier();  // every wavefront is past its reads of this tile's rows
-      ring_add(ring_kp, adq, rowvalid, kk, [&](auto PC) __attribute__((always_inline)) {
+      ring_add(ring_kp, adq, rowvalid, kk, col, [&](auto PC) __attribute__((always_inline)) {
         reduce_lanes32_level<NV, decltype(PC)::value + 1>(xv, lane);
       });
       {
         constexpr int NO = NV / 32;  // sums per lane: columns j0 .. j0 + NO - 1
         const int j0 = NV / 2 * ((c >> 4) & 1) + NV / 4 * ((c >> 3) & 1) + NV / 8 * ((c >> 2) & 1) +
                        NV / 16 * ((c >> 1) & 1) + NV / 32 * (c & 1);
-        // j = 16 dt + 4 qd + e  <->  d = 32 dt + 8 qd + 4 h + e
-        const int d0 = 32 * (j0 >> 4) + 8 * ((j0 >> 2) & 3) + 4 * h + (j0 & 3);
+        const int d0 = col(j0 >> 2) + (j0 & 3);
         if (qvalid) {
           uint16_t* dst = dq + base + static_cast<size_t>(i) * rs + d0;
           if constexpr (NO == 2) {
@@ -619,7 +731,7 @@ bool mfma_bwd_query_supported(const Shape& s) { return s.w2 <= 32 && (s.D == 64 
 hipError_t mfma_bwd_query(const Shape& s, const BwdPlan& plan, const void* q, const void* k,
                           const void* kp, const void* v, const void* vp, const void* dout,
                           const float* lse, const float* delta, void* dq, void* dkp, void* dvp,
-                          float* halo, float* dqt, hipStream_t st) {
+                          float* halo, hipStream_t st) {
   const long tot = static_cast<long>(plan.nchunks) * s.B * s.H;
   const dim3 grid(static_cast<unsigned>(((tot + 7) / 8) * 8));
   const auto* Q = static_cast<const uint16_t*>(q);
@@ -632,7 +744,7 @@ hipError_t mfma_bwd_query(const Shape& s, const BwdPlan& plan, const void* q, co
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, dim3(kQThreads), 0, st, s, plan, Q, K, KP, V, VP, DO, lse, delta,
                        static_cast<uint16_t*>(dq), static_cast<uint16_t*>(dkp), static_cast<uint16_t*>(dvp),
-                       halo, dqt);
+                       halo);
   };
   if (s.form == 1) {
     if (s.D == 128)

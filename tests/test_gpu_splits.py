@@ -59,3 +59,24 @@ def test_backward_splits_agree(kind, n, d, w1, w2, group):
         # same products, float32 sums in another order, one bf16 rounding: 2^-8 of
         # the element, and the order's error against the tensor's largest element
         assert bool(((a - c).abs() <= 2.0 ** -8 * a.abs() + 2.0 ** -12 * a.abs().max()).all())
+
+
+@pytest.mark.parametrize("d,w2", [(64, 5), (128, 5), (64, 31), (128, 31)])
+def test_determinant_rows_outside_the_window_stay_out(d, w2):
+    """The determinant backward's dq and dk' epilogue: a k' row that is not finite
+    reaches no query past its window, bit for bit (rows of a query's 32 that are
+    no pair's must not enter its sums, not even as zero times that row)."""
+    print(f"\n[det rows] D={d} w2={w2}", flush=True)
+    n, w1 = 150, 40
+    q, k, kp, v, vp, do = (x.cuda() for x in draw((1, n, 2, d), seed=900 + d + w2))
+    bad = kp.clone()
+    bad[:, 0] = float("nan")
+    runs = []
+    for x in (kp, bad):
+        o, lse = simplicial_attn_det_fwd(q, k, x, v, vp, w1, w2, d ** -0.5)
+        g = simplicial_attn_det_bwd(q, k, x, v, vp, o, do, lse, w1, w2, d ** -0.5)
+        torch.cuda.synchronize()
+        runs.append((o, g[0], g[2]))
+    for a, c in zip(*runs):
+        assert torch.isfinite(a).all()
+        assert torch.equal(a[:, w2:], c[:, w2:])
