@@ -19,7 +19,8 @@
 //
 // Measured, forward + backward: float32, B=1 H=4 N=2000 D=64 w1=256 w2=16, 16.8 ms
 // on the plain kernels (one thread per pair, operands read per pair), 0.50 ms
-// here; bf16, N=1024 D=128 w1=w2=128, 44.8 ms and 2.55 ms. The matrix cores are
+// here; bf16, N=1024 D=128 w1=w2=128, 44.8 ms and 2.55 ms (1.94 ms with the
+// forward and the query side on bf16 parts, below). The matrix cores are
 // busy 60% of the time at these sizes. Vector instructions are what costs the
 // rest: they add to the products' time even with two wavefronts per SIMD (6.9
 // per product: 0.54 ms; masks and operand checks on the edge blocks only: 0.50 ms), while loads issued further ahead of their use
@@ -163,6 +164,64 @@ __device__ __forceinline__ int tr_col(int c) {
   return (D < 32 ? c & (D - 1) : c) * static_cast<int>(sizeof(T));
 }
 
+// bf16 operands are exact in bf16, and a float32 value is the sum of three bf16
+// values (24 bits cut into 8, 8 and 8; the cuts toward zero are exact). So a
+// product of bf16 data with float32 values (q~, P, dS, do~) is three bf16
+// products of 16 contractions each: the same exact terms in float32 sums at
+// 16 / 3 of the float32 products' rate. Infinities and NaN do not split (an
+// infinity's remainder is NaN, and parts that are 0 turn an infinite operand
+// into NaN): kernels whose sums come out non-finite walk their blocks again
+// with float32 products. B=1 H=4 N=1024 D=128 w1=w2=128: forward and query side
+// together 1.43 -> 0.92 ms; LSE against 64 bits 5.2e-8 -> 4.9e-8.
+template <typename T>
+constexpr bool kSplit = sizeof(T) == 2;
+// (a product of two bf16 values is the sum of two parts)
+template <int NP>
+struct Parts8 {
+  u32x4_t p[NP];
+};
+template <int NP = 3>
+__device__ __forceinline__ Parts8<NP> split8(const float* x) {
+  Parts8<NP> r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float a = x[2 * i], b = x[2 * i + 1];
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+      const unsigned ua = __float_as_uint(a), ub = __float_as_uint(b);
+      r.p[n][i] = __builtin_amdgcn_perm(ub, ua, 0x07060302);  // the upper halves
+      a -= __uint_as_float(ua & 0xffff0000u);
+      b -= __uint_as_float(ub & 0xffff0000u);
+    }
+  }
+  return r;
+}
+template <int NP>
+__device__ __forceinline__ f32x16_t mfma_parts(u32x4_t a, const Parts8<NP>& b, f32x16_t c) {
+#pragma unroll
+  for (int n = NP - 1; n >= 0; --n) c = mfma32(a, b.p[n], c);
+  return c;
+}
+// Operand of 16 contractions: float4s 2 u and 2 u + 1 of a row chunk, or rows
+// 8 u .. 8 u + 7 (per lane half) of a transposed one.
+template <typename T, int D>
+__device__ __forceinline__ u32x4_t frag(const RowChunk<T, D>& r, int u) {
+  if constexpr (kSplit<T>)
+    return u32x4_t{r.x[2 * u].a[0], r.x[2 * u].a[1], r.x[2 * u + 1].a[0], r.x[2 * u + 1].a[1]};
+  else
+    return u32x4_t{};
+}
+template <typename T>
+__device__ __forceinline__ u32x4_t frag(const TrChunk<T>& r, int u) {
+  u32x4_t y = {};
+  if constexpr (kSplit<T>) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      y[e] = static_cast<unsigned>(r.x[8 * u + 2 * e]) | static_cast<unsigned>(r.x[8 * u + 2 * e + 1]) << 16;
+  }
+  return y;
+}
+
 // Sum / maximum over the 2^lw lanes (8, 16 or 32 of a half-wavefront) that hold
 // the k-rows of one query; every lane gets it.
 template <int LW, typename Op>
@@ -202,6 +261,16 @@ __device__ __forceinline__ bool any_nonfinite(const f32x16_t& u) {
   float x = 0.f;
 #pragma unroll
   for (int v = 0; v < 16; ++v) x += u[v];
+  return __builtin_amdgcn_ballot_w64(nonfinite(x)) != 0;
+}
+
+// Whether any lane's `x` or accumulators do.
+template <int N>
+__device__ __forceinline__ bool nonfinite_sums(float x, const f32x16_t (&u)[N]) {
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) x += u[n][v];
   return __builtin_amdgcn_ballot_w64(nonfinite(x)) != 0;
 }
 
@@ -284,7 +353,15 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
     const int t0 = (c & ((1 << lw) - 1)) + 32 * g;
     const int kk = i - t0;
     const bool rowvalid = i < N && t0 < w2 && kk >= 0;
+    float m, l;
+    f32x16_t acc[NDT];
+    // The group's key window; `split`: float32 values as three bf16 parts.
+    auto walk = [&](auto SPLIT) __attribute__((always_inline)) {
+    constexpr bool split = decltype(SPLIT)::value;
+    m = -INFINITY;
+    l = 0.f;
     float qt[4 * Ge::NF];
+    Parts8<3> qp[split ? Ge::NF / 2 : 1];
     {
       const T* qr = q + base + static_cast<size_t>(min(i, N - 1)) * rs + 4 * h;
       const T* kr = kp + basek + static_cast<size_t>(max(min(kk, N - 1), 0)) * rsk + 4 * h;
@@ -294,9 +371,11 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
 #pragma unroll
         for (int e = 0; e < 4; ++e) qt[4 * t + e] = rowvalid ? a.at(e) * qscale * (x.at(e) + s.kp_bias) : 0.f;
       }
+      if constexpr (split) {
+#pragma unroll
+        for (int t = 0; t < Ge::NF / 2; ++t) qp[t] = split8(qt + 8 * t);
+      }
     }
-    float m = -INFINITY, l = 0.f;
-    f32x16_t acc[NDT];
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt) acc[dt] = f32x16_t{};
     __amdgpu_buffer_rsrc_t bk = rows_from<T, D>(kb, jlo, N, rsb);
@@ -312,10 +391,15 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
           nx = load_rows<T, D>(bk, roff, ch + 1);
         else
           vc = load_tr<T>(bv, toff, rsb, 0);
+        if constexpr (split) {
 #pragma unroll
-        for (int t = 0; t < Ge::RC; ++t)
+          for (int u = 0; u < Ge::RC / 2; ++u) sc = mfma_parts(frag<T, D>(kc, u), qp[ch * Ge::RC / 2 + u], sc);
+        } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) sc = mfma_f32(kc.x[t].at(e), qt[4 * (ch * Ge::RC + t) + e], sc);
+          for (int t = 0; t < Ge::RC; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sc = mfma_f32(kc.x[t].at(e), qt[4 * (ch * Ge::RC + t) + e], sc);
+        }
         kc = nx;
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -346,6 +430,8 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
         l += p[vv];
       }
       bk = rows_from<T, D>(kb, jb + 32, N, rsb);  // the next block's
+      Parts8<3> pp[split ? 2 : 1];
+      if constexpr (split) pp[0] = split8(p), pp[1] = split8(p + 8);
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) {
         const TrChunk<T> cur = vc;
@@ -354,12 +440,18 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
         else
           kc = load_rows<T, D>(bk, roff, 0);
         f32x16_t u = {};
+        if constexpr (split) {
 #pragma unroll
-        for (int vv = 0; vv < 16; ++vv) {
-          const float y = to_f32(cur.x[vv]);
-          u = mfma_f32(D >= 32 || c < D ? y : 0.f, p[vv], u);
+          for (int n = 0; n < 2; ++n)
+            u = mfma_parts(D >= 32 || c < D ? frag<T>(cur, n) : u32x4_t{}, pp[n], u);
+        } else {
+#pragma unroll
+          for (int vv = 0; vv < 16; ++vv) {
+            const float y = to_f32(cur.x[vv]);
+            u = mfma_f32(D >= 32 || c < D ? y : 0.f, p[vv], u);
+          }
         }
-        if (edge && any_nonfinite(u))
+        if (!split && edge && any_nonfinite(u))
           u = masked_tile<D>(
               p, scratch[wave], c, h, [&](int x) { return jb + x >= lo && jb + x <= i; },
               [&](int x, int d, float* y) {
@@ -370,6 +462,11 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
         acc[dt] = acc[dt] * alpha + u;
         __builtin_amdgcn_sched_barrier(0);
       }
+    }
+    };
+    walk(std::bool_constant<kSplit<T>>{});
+    if constexpr (kSplit<T>) {
+      if (nonfinite_sums(l, acc)) walk(std::false_type{});
     }
     // Merge this group's rows into the query's O, M, L.
     const float lsum = l + swap_halves(l);
@@ -428,7 +525,6 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
     T* __restrict__ dvp, float* __restrict__ ws) {
   using Ge = Geo<D>;
   constexpr int NDT = Ge::NDT, RS = D + 4;
-  constexpr bool FLY = D >= 64;
   // Per wavefront kScratch floats (masked_tile's, or its dq rows at the end of a
   // step), then the rings (as many rows as w2 asks for).
   extern __shared__ __attribute__((aligned(16))) float f32_lds[];
@@ -508,6 +604,9 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
     const int jlo = max(0, i0 - w1 + 1), jhi = min(i0 + SP - 1, N - 1);
     const int ic = min(i, N - 1), kc_ = max(min(kk, N - 1), 0);
     f32x16_t au[NDT], aq[NDT];
+    // The rows' key window; `split`: float32 values as three bf16 parts.
+    auto walk = [&](auto SPLIT) __attribute__((always_inline)) {
+    constexpr bool split = decltype(SPLIT)::value, FLY = D >= 64 && !split;
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt) {
       au[dt] = f32x16_t{};
@@ -523,7 +622,9 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
       const __amdgpu_buffer_rsrc_t bkp = rows_from<T, D>(kp + base, k0, N, rsb), bvp = rows_from<T, D>(vp + base, k0, N, rsb);
       const int ro = (c >> lw) * rsb + 4 * h * static_cast<int>(sizeof(T));
       const int ko = rowvalid ? (kk - k0) * rsb + 4 * h * static_cast<int>(sizeof(T)) : kFar;
-      float qt[FLY ? 1 : 4 * Ge::NF], ot[FLY ? 1 : 4 * Ge::NF];
+      float qt[FLY || split ? 1 : 4 * Ge::NF], ot[FLY || split ? 1 : 4 * Ge::NF];
+      Parts8<3> qp[split ? Ge::NF / 2 : 1];
+      Parts8<BIAS ? 3 : 2> op[split ? Ge::NF / 2 : 1];
       // (a row outside the window or the sequence loads k', v' as zeros; its S
       // and dP are masked below)
       auto form = [&](const RowChunk<T, D>& a, const RowChunk<T, D>& x, bool scaled, float bias, float* y) {
@@ -533,7 +634,18 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
           for (int e = 0; e < 4; ++e)
             y[4 * t + e] = (scaled ? a.x[t].at(e) * qscale : a.x[t].at(e)) * plus_bias<BIAS>(x.x[t].at(e), bias);
       };
-      if constexpr (!FLY) {
+      if constexpr (split) {
+#pragma unroll
+        for (int ch = 0; ch < Ge::NRC; ++ch) {
+          float y[4 * Ge::RC];
+          form(load_rows<T, D>(bq, ro, ch), load_rows<T, D>(bkp, ko, ch), true, s.kp_bias, y);
+#pragma unroll
+          for (int u = 0; u < Ge::RC / 2; ++u) qp[ch * Ge::RC / 2 + u] = split8(y + 8 * u);
+          form(load_rows<T, D>(bg, ro, ch), load_rows<T, D>(bvp, ko, ch), false, s.vp_bias, y);
+#pragma unroll
+          for (int u = 0; u < Ge::RC / 2; ++u) op[ch * Ge::RC / 2 + u] = split8<BIAS ? 3 : 2>(y + 8 * u);
+        }
+      } else if constexpr (!FLY) {
 #pragma unroll
         for (int ch = 0; ch < Ge::NRC; ++ch) {
           form(load_rows<T, D>(bq, ro, ch), load_rows<T, D>(bkp, ko, ch), true, s.kp_bias, qt + 4 * Ge::RC * ch);
@@ -558,7 +670,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
             float y[4 * Ge::RC];
             if constexpr (FLY) {
               form(fa, fm, ph == 0, ph ? s.vp_bias : s.kp_bias, y);
-            } else {
+            } else if constexpr (!split) {
 #pragma unroll
               for (int e = 0; e < 4 * Ge::RC; ++e) y[e] = (ph ? ot : qt)[4 * Ge::RC * ch + e];
             }
@@ -574,15 +686,18 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
                 fm = load_rows<T, D>(second ? bvp : bkp, ko, nch);
               }
             }
+            f32x16_t& acc = ph ? dp : sc;
+            if constexpr (split) {
 #pragma unroll
-            for (int t = 0; t < Ge::RC; ++t)
+              for (int u = 0; u < Ge::RC / 2; ++u)
+                acc = ph ? mfma_parts(frag<T, D>(cur, u), op[ch * Ge::RC / 2 + u], acc)
+                         : mfma_parts(frag<T, D>(cur, u), qp[ch * Ge::RC / 2 + u], acc);
+            } else {
 #pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                if (ph)
-                  dp = mfma_f32(cur.x[t].at(e), y[4 * t + e], dp);
-                else
-                  sc = mfma_f32(cur.x[t].at(e), y[4 * t + e], sc);
-              }
+              for (int t = 0; t < Ge::RC; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc = mfma_f32(cur.x[t].at(e), y[4 * t + e], acc);
+            }
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -599,6 +714,8 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
         const bool edge = jb < i0 + SP - w1 || jb + 31 > i0;  // keys that not every query sees
         // U~^T += V^T P^T, dQ~^T += K^T dS^T
         const __amdgpu_buffer_rsrc_t bkc = bk;  // this block's (bk moves on below)
+        Parts8<3> pp[split ? 2 : 1], dsp[split ? 2 : 1];
+        if constexpr (split) pp[0] = split8(p), pp[1] = split8(p + 8), dsp[0] = split8(ds), dsp[1] = split8(ds + 8);
 #pragma unroll
         for (int x = 0; x < 2 * NDT; ++x) {
           const int dt = x % NDT;
@@ -614,12 +731,18 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
             }
           }
           f32x16_t u = {};
+          if constexpr (split) {
 #pragma unroll
-          for (int vv = 0; vv < 16; ++vv) {
-            const float y = to_f32(cur.x[vv]);
-            u = mfma_f32(D >= 32 || c < D ? y : 0.f, x < NDT ? p[vv] : ds[vv], u);
+            for (int n = 0; n < 2; ++n)
+              u = mfma_parts(D >= 32 || c < D ? frag<T>(cur, n) : u32x4_t{}, (x < NDT ? pp : dsp)[n], u);
+          } else {
+#pragma unroll
+            for (int vv = 0; vv < 16; ++vv) {
+              const float y = to_f32(cur.x[vv]);
+              u = mfma_f32(D >= 32 || c < D ? y : 0.f, x < NDT ? p[vv] : ds[vv], u);
+            }
           }
-          if (edge && any_nonfinite(u))
+          if (!split && edge && any_nonfinite(u))
             u = masked_tile<D>(
                 x < NDT ? p : ds, scratch, c, h, [&](int y) { return rowvalid && jb + y >= lo && jb + y <= i; },
                 [&](int y, int d, float* z) {
@@ -635,6 +758,11 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
           __builtin_amdgcn_sched_barrier(0);
         }
       }
+    }
+    };
+    walk(std::bool_constant<kSplit<T>>{});
+    if constexpr (kSplit<T>) {
+      if (nonfinite_sums(0.f, au) || nonfinite_sums(0.f, aq)) walk(std::false_type{});
     }
     // ---- end of the step: dq, then the k-row contributions ----
     if (busy) {

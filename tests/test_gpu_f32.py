@@ -117,3 +117,34 @@ def test_f32_rows_outside_the_window_do_not_matter(w2, d):
                  2: (idx <= lo - w2) | (idx > hi), 4: (idx <= lo - w2) | (idx > hi)}
         for gi, keep in reach.items():
             assert torch.allclose(g2[gi][0, keep], g[gi][0, keep], rtol=1e-4, atol=1e-5), (name, gi)
+
+
+@pytest.mark.parametrize("d,w2,n", [(16, 8, 70), (32, 32, 131), (64, 65, 90), (128, 128, 160), (128, 97, 75)])
+@pytest.mark.parametrize("bad", ["", "k", "v", "q", "do"])
+def test_bf16_products_in_parts_equal_float32(d, w2, n, bad):
+    """bf16 data multiplies float32 values as three bf16 parts: the same sums as
+    with float32 products of the widened data (the float32 entry), so the LSE
+    agrees to float32 rounding, outputs to one bf16 rounding (2^-8), and
+    infinities give the same infinities and NaN."""
+    w1, scale = 40, d ** -0.5
+    print(f"\n[f32] parts D={d} w2={w2} N={n} infinity in {bad or 'nothing'}", flush=True)
+    x = [t.cuda() for t in draw((1, n, 2, d), seed=n + w2, dtype=torch.bfloat16)]
+    o, lse = simplicial_attn_fwd(*x[:5], w1, w2, scale)
+    if bad:
+        x[("q", "k", "kp", "v", "vp", "do").index(bad)][0, n // 2, 1, d // 3] = float("inf")
+    wide = [t.float() for t in x]
+    got = [*simplicial_attn_fwd(*x[:5], w1, w2, scale),
+           *simplicial_attn_bwd(*x[:5], o, x[5], lse, w1, w2, scale)]
+    ref = [*simplicial_attn_fwd(*wide[:5], w1, w2, scale),
+           *simplicial_attn_bwd(*wide[:5], o.float(), wide[5], lse, w1, w2, scale)]
+    torch.cuda.synchronize()
+    for t, (a, r) in enumerate(zip(got, ref)):
+        assert torch.equal(torch.isfinite(a), torch.isfinite(r)), t
+        assert torch.equal(torch.isnan(a), torch.isnan(r)), t
+        ok = torch.isfinite(r)
+        big = float(r[ok].abs().max()) if bool(ok.any()) else 0.0
+        err = (a.float()[ok] - r[ok]).abs()
+        # LSE: a few float32 roundings of sums of up to 5120 terms; the others one
+        # bf16 rounding plus float32 sums of the size of the largest
+        bound = 4e-6 * max(big, 1.0) if t == 1 else 2.0 ** -8 * r[ok].abs() + 4e-6 * big
+        assert bool((err <= bound).all()), (t, float(err.max()))
