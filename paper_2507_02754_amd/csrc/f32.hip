@@ -19,8 +19,8 @@
 //
 // Measured, forward + backward: float32, B=1 H=4 N=2000 D=64 w1=256 w2=16, 16.8 ms
 // on the plain kernels (one thread per pair, operands read per pair), 0.50 ms
-// here; bf16, N=1024 D=128 w1=w2=128, 44.8 ms and 2.55 ms (1.94 ms with the
-// forward and the query side on bf16 parts, below). The matrix cores are
+// here; bf16, N=1024 D=128 w1=w2=128, 44.8 ms and 2.55 ms (1.62 ms on
+// bf16 parts, below). The matrix cores are
 // busy 60% of the time at these sizes. Vector instructions are what costs the
 // rest: they add to the products' time even with two wavefronts per SIMD (6.9
 // per product: 0.54 ms; masks and operand checks on the edge blocks only: 0.50 ms), while loads issued further ahead of their use
@@ -172,7 +172,8 @@ __device__ __forceinline__ int tr_col(int c) {
 // infinity's remainder is NaN, and parts that are 0 turn an infinite operand
 // into NaN): kernels whose sums come out non-finite walk their blocks again
 // with float32 products. B=1 H=4 N=1024 D=128 w1=w2=128: forward and query side
-// together 1.43 -> 0.92 ms; LSE against 64 bits 5.2e-8 -> 4.9e-8.
+// together 1.43 -> 0.92 ms, key side (do~ and q~ without scale, products of two
+// bf16 values, times P and dS: two parts by three) 1.10 -> 0.77 ms; LSE against 64 bits 5.2e-8 -> 4.9e-8.
 template <typename T>
 constexpr bool kSplit = sizeof(T) == 2;
 // (a product of two bf16 values is the sum of two parts)
@@ -200,6 +201,12 @@ template <int NP>
 __device__ __forceinline__ f32x16_t mfma_parts(u32x4_t a, const Parts8<NP>& b, f32x16_t c) {
 #pragma unroll
   for (int n = NP - 1; n >= 0; --n) c = mfma32(a, b.p[n], c);
+  return c;
+}
+template <int NP>
+__device__ __forceinline__ f32x16_t mfma_parts(const Parts8<NP>& a, u32x4_t b, f32x16_t c) {
+#pragma unroll
+  for (int n = NP - 1; n >= 0; --n) c = mfma32(a.p[n], b, c);
   return c;
 }
 // Operand of 16 contractions: float4s 2 u and 2 u + 1 of a row chunk, or rows
@@ -895,6 +902,7 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
   using Ge = Geo<D>;
   constexpr int NDT = Ge::NDT, RS = D + 4, KW = key_waves<D>();
   // K and V operands, then masked_tile scratch; at the end the wavefronts' sums.
+  constexpr int kPer = kSplit<T> ? 2 : 1;  // float4s of an operand in 16 bytes
   constexpr int kOps = 2 * 32 * D, kScr = KW * kScratch, kSum = KW * 32 * RS;
   __shared__ __attribute__((aligned(16))) float lds[kSum > kOps + kScr ? kSum : kOps + kScr];
   const int SP = 32 >> lw;
@@ -918,21 +926,36 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
   const int rsb = static_cast<int>(rs * sizeof(T));
 
   // K and V rows as operands, in the order the products take them: float4 t of
-  // lane (h, c) (key j0 + c, columns 8 t + 4 h .. + 3) at 64 t + lane.
-  float4* const opk = reinterpret_cast<float4*>(lds) + lane;
-  float4* const opv = opk + 64 * Ge::NF;
+  // lane (h, c) (key j0 + c, columns 8 t + 4 h .. + 3) at 64 t + lane; bf16: 2 t
+  // and 2 t + 1 there (frag's order).
+  u32x4_t* const opk = reinterpret_cast<u32x4_t*>(lds) + lane;
+  u32x4_t* const opv = opk + 64 * Ge::NF;
   {
     const __amdgpu_buffer_rsrc_t rk = rows_from<T, D>(k + base, j0, N, rsb), rv = rows_from<T, D>(v + base, j0, N, rsb);
     const int off = c * rsb + 4 * h * static_cast<int>(sizeof(T));
-    for (int t = wave; t < Ge::NF; t += KW) {
-      const Raw4<T> a = ldb4<T>(rk, off + 8 * t * static_cast<int>(sizeof(T)));
-      const Raw4<T> y = ldb4<T>(rv, off + 8 * t * static_cast<int>(sizeof(T)));
-      opk[64 * t] = float4{a.at(0), a.at(1), a.at(2), a.at(3)};
-      opv[64 * t] = float4{y.at(0), y.at(1), y.at(2), y.at(3)};
+    for (int t = wave; t < Ge::NF / kPer; t += KW) {
+      Raw4<T> a[kPer], y[kPer];
+#pragma unroll
+      for (int n = 0; n < kPer; ++n) {
+        a[n] = ldb4<T>(rk, off + 8 * (kPer * t + n) * static_cast<int>(sizeof(T)));
+        y[n] = ldb4<T>(rv, off + 8 * (kPer * t + n) * static_cast<int>(sizeof(T)));
+      }
+      opk[64 * t] = __builtin_bit_cast(u32x4_t, a);
+      opv[64 * t] = __builtin_bit_cast(u32x4_t, y);
     }
   }
   __syncthreads();
+  // Element e of float4 t of such an operand.
+  auto op_at = [&](const u32x4_t& w, int t, int e) {
+    if constexpr (kSplit<T>)
+      return Raw4<uint16_t>{u32x2_t{w[2 * (t & 1)], w[2 * (t & 1) + 1]}}.at(e);
+    else
+      return __uint_as_float(w[e]);
+  };
   f32x16_t ak[NDT], av[NDT];
+  // The row blocks of the key window; `split`: float32 values as bf16 parts.
+  auto walk = [&](auto SPLIT) __attribute__((always_inline)) {
+  constexpr bool split = decltype(SPLIT)::value;
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt) {
     ak[dt] = f32x16_t{};
@@ -971,13 +994,22 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
     for (int ch = 0; ch < Ge::NRC; ++ch) {
       const RowChunk<T, D> na = ch + 1 < Ge::NRC ? load_rows<T, D>(bq, ro, ch + 1) : load_rows<T, D>(bg, ro, 0);
       const RowChunk<T, D> nm = ch + 1 < Ge::NRC ? load_rows<T, D>(bkp, ko, ch + 1) : load_rows<T, D>(bvp, ko, 0);
+      float x[4 * Ge::RC];
 #pragma unroll
-      for (int t = 0; t < Ge::RC; ++t) {
-        const float4 w = opk[64 * (ch * Ge::RC + t)];
+      for (int t = 0; t < Ge::RC; ++t)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float x = a.x[t].at(e) * qscale * plus_bias<BIAS>(m.x[t].at(e), s.kp_bias);
-          sc = mfma_f32(x, e == 0 ? w.x : e == 1 ? w.y : e == 2 ? w.z : w.w, sc);
+        for (int e = 0; e < 4; ++e)
+          x[4 * t + e] = a.x[t].at(e) * qscale * plus_bias<BIAS>(m.x[t].at(e), s.kp_bias);
+      if constexpr (split) {
+#pragma unroll
+        for (int u = 0; u < Ge::RC / 2; ++u)
+          sc = mfma_parts(split8(x + 8 * u), opk[64 * (ch * Ge::RC / 2 + u)], sc);
+      } else {
+#pragma unroll
+        for (int t = 0; t < Ge::RC; ++t) {
+          const u32x4_t w = opk[64 * ((ch * Ge::RC + t) / kPer)];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sc = mfma_f32(x[4 * t + e], op_at(w, t, e), sc);
         }
       }
       a = na;
@@ -1015,13 +1047,21 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
         load_q(bg, 0, ta);
         tm = load_k(bvp, 0);
       }
+      float x[4 * Ge::RC];
 #pragma unroll
-      for (int t = 0; t < Ge::RC; ++t) {
-        const float4 w = opv[64 * (ch * Ge::RC + t)];
+      for (int t = 0; t < Ge::RC; ++t)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float x = a.x[t].at(e) * plus_bias<BIAS>(m.x[t].at(e), s.vp_bias);
-          dp = mfma_f32(x, e == 0 ? w.x : e == 1 ? w.y : e == 2 ? w.z : w.w, dp);
+        for (int e = 0; e < 4; ++e) x[4 * t + e] = a.x[t].at(e) * plus_bias<BIAS>(m.x[t].at(e), s.vp_bias);
+      if constexpr (split) {
+#pragma unroll
+        for (int u = 0; u < Ge::RC / 2; ++u)
+          dp = mfma_parts(split8<BIAS ? 3 : 2>(x + 8 * u), opv[64 * (ch * Ge::RC / 2 + u)], dp);
+      } else {
+#pragma unroll
+        for (int t = 0; t < Ge::RC; ++t) {
+          const u32x4_t w = opv[64 * ((ch * Ge::RC + t) / kPer)];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dp = mfma_f32(x[4 * t + e], op_at(w, t, e), dp);
         }
       }
       a = na;
@@ -1052,6 +1092,8 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
       const int i = i0 + (r >> lw);
       return tof(r) < lim(r >> lw) && j <= i && j > i - w1 && j < N;
     };
+    Parts8<3> pp[split ? 2 : 1], dsp[split ? 2 : 1];
+    if constexpr (split) pp[0] = split8(p), pp[1] = split8(p + 8), dsp[0] = split8(ds), dsp[1] = split8(ds + 8);
     // dV^T += do~^T P, dK^T += q~^T dS (unscaled q~)
 #pragma unroll
     for (int x = 0; x < 2 * NDT; ++x) {
@@ -1064,12 +1106,24 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
       }
       const float bias = x < NDT ? s.vp_bias : s.kp_bias;
       f32x16_t u = {};
+      float y[16];
 #pragma unroll
       for (int vv = 0; vv < 16; ++vv) {
-        const float y = to_f32(ca[vv >> 2]) * plus_bias<BIAS>(to_f32(cm.x[vv]), bias);
-        u = mfma_f32(D >= 32 || c < D ? y : 0.f, x < NDT ? p[vv] : ds[vv], u);
+        y[vv] = to_f32(ca[vv >> 2]) * plus_bias<BIAS>(to_f32(cm.x[vv]), bias);
+        if (D < 32) y[vv] = c < D ? y[vv] : 0.f;
       }
-      if (edge && any_nonfinite(u))
+      if constexpr (split) {
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          const auto yp = split8<BIAS ? 3 : 2>(y + 8 * n);
+#pragma unroll
+          for (int o = (BIAS ? 3 : 2) - 1; o >= 0; --o) u = mfma_parts(yp.p[o], (x < NDT ? pp : dsp)[n], u);
+        }
+      } else {
+#pragma unroll
+        for (int vv = 0; vv < 16; ++vv) u = mfma_f32(y[vv], x < NDT ? p[vv] : ds[vv], u);
+      }
+      if (!split && edge && any_nonfinite(u))
         u = masked_tile<D>(x < NDT ? p : ds, lds + kOps + wave * kScratch, c, h, seen, [&](int r, int d, float* z) {
           const int at = (32 * dt + d) * static_cast<int>(sizeof(T));
           const Raw4<T> y0 = ldb4<T>(x < NDT ? bg : bq, (r >> lw) * rsb + at);
@@ -1083,6 +1137,11 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
         ak[dt] += u;
       __builtin_amdgcn_sched_barrier(0);
     }
+  }
+  };
+  walk(std::bool_constant<kSplit<T>>{});
+  if constexpr (kSplit<T>) {
+    if (nonfinite_sums(0.f, ak) || nonfinite_sums(0.f, av)) walk(std::false_type{});
   }
   // ---- sum of the wavefronts, dV then dK ----
 #pragma unroll
