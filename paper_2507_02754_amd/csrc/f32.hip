@@ -19,7 +19,7 @@
 //
 // Measured, forward + backward: float32, B=1 H=4 N=2000 D=64 w1=256 w2=16, 16.8 ms
 // on the plain kernels (one thread per pair, operands read per pair), 0.50 ms
-// here; bf16, N=1024 D=128 w1=w2=128, 44.8 ms and 2.55 ms (1.62 ms on
+// here; bf16, N=1024 D=128 w1=w2=128, 44.8 ms and 2.55 ms (1.55 ms on
 // bf16 parts, below). The matrix cores are
 // busy 60% of the time at these sizes. Vector instructions are what costs the
 // rest: they add to the products' time even with two wavefronts per SIMD (6.9
@@ -131,10 +131,98 @@ template <typename T, int D>
 struct RowChunk {
   Raw4<T> x[Geo<D>::RC];
 };
-// One accumulator tile's operand: the lane's column of rows acc_row(v, h).
-template <typename T>
+// Columns of the accumulator tiles: row m of tile dt is column 32 dt + m, or for
+// bf16 data of several tiles NDT m + dt, so that one load of a row (8 bytes a
+// lane at head_dim 128) serves every tile of a transposed operand: a quarter of
+// the load instructions, 1.62 -> 1.55 ms at B=1 H=4 N=1024 w1=w2=128.
+template <typename T, int D>
+constexpr bool kWide = sizeof(T) == 2 && D >= 64;
+template <typename T, int D>
+struct Wide {
+  using W = T;  // what a lane loads of a row
+};
+template <>
+struct Wide<uint16_t, 64> {
+  using W = unsigned;
+};
+template <>
+struct Wide<uint16_t, 128> {
+  using W = u32x2_t;
+};
+template <typename T, int D>
+__device__ __forceinline__ typename Wide<T, D>::W ldw(__amdgpu_buffer_rsrc_t r, int off) {
+  if constexpr (!kWide<T, D>)
+    return ldb1<T>(r, off);
+  else if constexpr (D == 64)
+    return ldbuf32(r, off);
+  else
+    return ldbuf64(r, off);
+}
+template <typename T, int D>
+__device__ __forceinline__ unsigned word(const typename Wide<T, D>::W& w, int dt) {
+  if constexpr (D == 128)
+    return w[dt >> 1];
+  else
+    return w;
+}
+// Element of tile dt, in float32.
+template <typename T, int D>
+__device__ __forceinline__ float elem(const typename Wide<T, D>::W& w, int dt) {
+  if constexpr (kWide<T, D>)
+    return (dt & 1) ? bf16_hi(word<T, D>(w, dt)) : bf16_lo(word<T, D>(w, dt));
+  else
+    return to_f32(w);
+}
+// Column of row m of tile dt, and 32 dt + m of column d.
+template <typename T, int D>
+__device__ __forceinline__ int column(int dt, int m) {
+  return kWide<T, D> ? Geo<D>::NDT * m + dt : 32 * dt + m;
+}
+template <typename T, int D>
+__device__ __forceinline__ int place(int d) {
+  return kWide<T, D> ? 32 * (d % Geo<D>::NDT) + d / Geo<D>::NDT : d;
+}
+// One accumulator tile's operand (kWide: every tile's): the lane's column of
+// rows acc_row(v, h).
+template <typename T, int D>
 struct TrChunk {
-  T x[16];
+  typename Wide<T, D>::W x[16];
+};
+// Rows d .. d + 3 of tile dt: the columns of one row of a tensor.
+template <typename T, int D>
+__device__ __forceinline__ void ldcols(__amdgpu_buffer_rsrc_t b, int off, int dt, int d, float* z) {
+  if constexpr (kWide<T, D>) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      z[e] = to_f32(ldb1<T>(b, off + column<T, D>(dt, d + e) * static_cast<int>(sizeof(T))));
+  } else {
+    const Raw4<T> r = ldb4<T>(b, off + (32 * dt + d) * static_cast<int>(sizeof(T)));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) z[e] = r.at(e);
+  }
+}
+// A row in accumulator order: get gives rows 8 vq + 4 h .. + 3 of tile dt.
+template <typename T, int D>
+struct RowCols {
+  using W = typename Wide<T, D>::W;
+  const T* p;
+  W x[kWide<T, D> ? 16 : 1];
+  __device__ __forceinline__ RowCols(const T* row, int h) : p(row + 4 * h) {
+    if constexpr (kWide<T, D>) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) x[v] = *reinterpret_cast<const W*>(row + Geo<D>::NDT * acc_row(v, h));
+    }
+  }
+  __device__ __forceinline__ void get(int dt, int vq, float* z) const {
+    if constexpr (kWide<T, D>) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[e] = elem<T, D>(x[4 * vq + e], dt);
+    } else {
+      const Raw4<T> y = ld4(p + 32 * dt + 8 * vq);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[e] = y.at(e);
+    }
+  }
 };
 // Chunk ch of the lane's row at byte offset `off` (already at its half: + 4 h
 // elements).
@@ -146,22 +234,21 @@ __device__ __forceinline__ RowChunk<T, D> load_rows(__amdgpu_buffer_rsrc_t b, in
     r.x[t] = ldb4<T>(b, off + 8 * (ch * Geo<D>::RC + t) * static_cast<int>(sizeof(T)));
   return r;
 }
-// Tile dt of a transposed operand; `off` is the lane's offset at tile 0: 4 h
-// rows and tr_col().
-template <typename T>
-__device__ __forceinline__ TrChunk<T> load_tr(__amdgpu_buffer_rsrc_t b, int off, int rsb, int dt) {
-  TrChunk<T> r;
+// Tile dt of a transposed operand (kWide: every tile, with tile 0); `off` is the
+// lane's offset at tile 0: 4 h rows and tr_col().
+template <typename T, int D>
+__device__ __forceinline__ void load_tr(TrChunk<T, D>& r, __amdgpu_buffer_rsrc_t b, int off, int rsb, int dt) {
+  if (kWide<T, D> && dt > 0) return;
   asm volatile("" : "+v"(off));  // the sixteen offsets are formed here, not kept in registers
 #pragma unroll
   for (int v = 0; v < 16; ++v)
-    r.x[v] = ldb1<T>(b, off + acc_row(v, 0) * rsb + 32 * dt * static_cast<int>(sizeof(T)));
-  return r;
+    r.x[v] = ldw<T, D>(b, off + acc_row(v, 0) * rsb + 32 * dt * static_cast<int>(sizeof(T)));
 }
 // Byte offset of the lane's column in tile 0 (head_dim 16: the lanes past the
 // row repeat it; their operand is set to 0).
 template <typename T, int D>
 __device__ __forceinline__ int tr_col(int c) {
-  return (D < 32 ? c & (D - 1) : c) * static_cast<int>(sizeof(T));
+  return (D < 32 ? c & (D - 1) : c) * static_cast<int>(sizeof(typename Wide<T, D>::W));
 }
 
 // bf16 operands are exact in bf16, and a float32 value is the sum of three bf16
@@ -218,13 +305,14 @@ __device__ __forceinline__ u32x4_t frag(const RowChunk<T, D>& r, int u) {
   else
     return u32x4_t{};
 }
-template <typename T>
-__device__ __forceinline__ u32x4_t frag(const TrChunk<T>& r, int u) {
+template <typename T, int D>
+__device__ __forceinline__ u32x4_t frag(const TrChunk<T, D>& r, int u, int dt) {
   u32x4_t y = {};
   if constexpr (kSplit<T>) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      y[e] = static_cast<unsigned>(r.x[8 * u + 2 * e]) | static_cast<unsigned>(r.x[8 * u + 2 * e + 1]) << 16;
+      y[e] = __builtin_amdgcn_perm(word<T, D>(r.x[8 * u + 2 * e + 1], dt), word<T, D>(r.x[8 * u + 2 * e], dt),
+                                   kWide<T, D> && (dt & 1) ? 0x07060302 : 0x05040100);
   }
   return y;
 }
@@ -390,14 +478,14 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
     for (int jb = jlo; jb <= jhi; jb += 32) {
       const __amdgpu_buffer_rsrc_t bv = rows_from<T, D>(vb, jb, N, rsb);
       f32x16_t sc = {};
-      TrChunk<T> vc;
+      TrChunk<T, D> vc;
 #pragma unroll
       for (int ch = 0; ch < Ge::NRC; ++ch) {
         RowChunk<T, D> nx;
         if (ch + 1 < Ge::NRC)
           nx = load_rows<T, D>(bk, roff, ch + 1);
         else
-          vc = load_tr<T>(bv, toff, rsb, 0);
+          load_tr<T, D>(vc, bv, toff, rsb, 0);
         if constexpr (split) {
 #pragma unroll
           for (int u = 0; u < Ge::RC / 2; ++u) sc = mfma_parts(frag<T, D>(kc, u), qp[ch * Ge::RC / 2 + u], sc);
@@ -441,20 +529,20 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
       if constexpr (split) pp[0] = split8(p), pp[1] = split8(p + 8);
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) {
-        const TrChunk<T> cur = vc;
+        const TrChunk<T, D> cur = vc;
         if (dt + 1 < NDT)
-          vc = load_tr<T>(bv, toff, rsb, dt + 1);
+          load_tr<T, D>(vc, bv, toff, rsb, dt + 1);
         else
           kc = load_rows<T, D>(bk, roff, 0);
         f32x16_t u = {};
         if constexpr (split) {
 #pragma unroll
           for (int n = 0; n < 2; ++n)
-            u = mfma_parts(D >= 32 || c < D ? frag<T>(cur, n) : u32x4_t{}, pp[n], u);
+            u = mfma_parts(D >= 32 || c < D ? frag<T, D>(cur, n, dt) : u32x4_t{}, pp[n], u);
         } else {
 #pragma unroll
           for (int vv = 0; vv < 16; ++vv) {
-            const float y = to_f32(cur.x[vv]);
+            const float y = elem<T, D>(cur.x[vv], dt);
             u = mfma_f32(D >= 32 || c < D ? y : 0.f, p[vv], u);
           }
         }
@@ -462,9 +550,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
           u = masked_tile<D>(
               p, scratch[wave], c, h, [&](int x) { return jb + x >= lo && jb + x <= i; },
               [&](int x, int d, float* y) {
-                const Raw4<T> r = ldb4<T>(bv, x * rsb + (32 * dt + d) * static_cast<int>(sizeof(T)));
-#pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] = r.at(e);
+                ldcols<T, D>(bv, x * rsb, dt, d, y);
               });
         acc[dt] = acc[dt] * alpha + u;
         __builtin_amdgcn_sched_barrier(0);
@@ -477,7 +563,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
     }
     // Merge this group's rows into the query's O, M, L.
     const float lsum = l + swap_halves(l);
-    const T* vr = vp + basek + static_cast<size_t>(max(min(kk, N - 1), 0)) * rsk;
+    const RowCols<T, D> vr(vp + basek + static_cast<size_t>(max(min(kk, N - 1), 0)) * rsk, h);
     with_lw(lw, [&](auto LC) __attribute__((always_inline)) {
       constexpr int LW = decltype(LC)::value;
       const float mg = seg_reduce<LW>(rowvalid ? m : -INFINITY, OpMax());
@@ -489,10 +575,11 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
       for (int dt = 0; dt < NDT; ++dt) {
 #pragma unroll
         for (int vq = 0; vq < Ge::NV / 4; ++vq) {
-          const Raw4<T> y = ld4(vr + 32 * dt + 8 * vq + 4 * h);
+          float y[4];
+          vr.get(dt, vq, y);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float x = rowvalid ? w * (y.at(e) + s.vp_bias) * acc[dt][4 * vq + e] : 0.f;
+            const float x = rowvalid ? w * (y[e] + s.vp_bias) * acc[dt][4 * vq + e] : 0.f;
             float& oo = o[Ge::NV * dt + 4 * vq + e];
             oo = oo * a + seg_reduce<LW>(x, OpSum());
           }
@@ -506,7 +593,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-      for (int vv = 0; vv < Ge::NV; ++vv) st1(dst + 32 * dt + acc_row(vv, h), o[Ge::NV * dt + vv] / L);
+      for (int vv = 0; vv < Ge::NV; ++vv) st1(dst + column<T, D>(dt, acc_row(vv, h)), o[Ge::NV * dt + vv] / L);
     // ln 2 in two parts: the product with M is not rounded before the sum
     if (h == 0) lse[static_cast<size_t>(bh) * N + i] = __builtin_fmaf(M, kLn2, __builtin_fmaf(M, kLn2Lo, logf(L)));
   }
@@ -576,8 +663,8 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
     for (int x = tid; x < n * D; x += kFThreads) {
       const int kr = klo + x / D, d = x % D;
       const int row = (kr + WT) % RB;
-      float* a = ring_k + row * RS + d;
-      float* y = ring_v + row * RS + d;
+      float* a = ring_k + row * RS + place<T, D>(d);
+      float* y = ring_v + row * RS + place<T, D>(d);
       if (kr >= 0) {
         if (plan.full) {
           const size_t at = static_cast<size_t>(kr - (cs - WT + 1)) * D + d;
@@ -669,7 +756,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
         const __amdgpu_buffer_rsrc_t bv = rows_from<T, D>(vb, jb, N, rsb);
         // S^T and dP^T
         f32x16_t sc = {}, dp = {};
-        TrChunk<T> tc;
+        TrChunk<T, D> tc;
 #pragma unroll
         for (int ph = 0; ph < 2; ++ph) {
 #pragma unroll
@@ -685,7 +772,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
             const int nch = ch + 1 < Ge::NRC ? ch + 1 : 0;
             const bool second = ph == 1 || nch == 0;  // the next chunk is dP's
             if (ph == 1 && nch == 0) {
-              tc = load_tr<T>(bv, toff, rsb, 0);
+              load_tr<T, D>(tc, bv, toff, rsb, 0);
             } else {
               rc = load_rows<T, D>(second ? bv : bk, roff, nch);
               if constexpr (FLY) {
@@ -726,9 +813,9 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
 #pragma unroll
         for (int x = 0; x < 2 * NDT; ++x) {
           const int dt = x % NDT;
-          const TrChunk<T> cur = tc;
+          const TrChunk<T, D> cur = tc;
           if (x + 1 < 2 * NDT) {
-            tc = load_tr<T>(x + 1 < NDT ? bv : bkc, toff, rsb, (x + 1) % NDT);
+            load_tr<T, D>(tc, x + 1 < NDT ? bv : bkc, toff, rsb, (x + 1) % NDT);
           } else {
             bk = rows_from<T, D>(kb, jb + 32, N, rsb);
             rc = load_rows<T, D>(bk, roff, 0);
@@ -741,11 +828,11 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
           if constexpr (split) {
 #pragma unroll
             for (int n = 0; n < 2; ++n)
-              u = mfma_parts(D >= 32 || c < D ? frag<T>(cur, n) : u32x4_t{}, (x < NDT ? pp : dsp)[n], u);
+              u = mfma_parts(D >= 32 || c < D ? frag<T, D>(cur, n, dt) : u32x4_t{}, (x < NDT ? pp : dsp)[n], u);
           } else {
 #pragma unroll
             for (int vv = 0; vv < 16; ++vv) {
-              const float y = to_f32(cur.x[vv]);
+              const float y = elem<T, D>(cur.x[vv], dt);
               u = mfma_f32(D >= 32 || c < D ? y : 0.f, x < NDT ? p[vv] : ds[vv], u);
             }
           }
@@ -753,10 +840,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
             u = masked_tile<D>(
                 x < NDT ? p : ds, scratch, c, h, [&](int y) { return rowvalid && jb + y >= lo && jb + y <= i; },
                 [&](int y, int d, float* z) {
-                  const Raw4<T> r =
-                      ldb4<T>(x < NDT ? bv : bkc, y * rsb + (32 * dt + d) * static_cast<int>(sizeof(T)));
-#pragma unroll
-                  for (int e = 0; e < 4; ++e) z[e] = r.at(e);
+                  ldcols<T, D>(x < NDT ? bv : bkc, y * rsb, dt, d, z);
                 });
           if (x < NDT)
             au[dt] += u;
@@ -773,7 +857,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
     }
     // ---- end of the step: dq, then the k-row contributions ----
     if (busy) {
-      const T* kr = kp + base + static_cast<size_t>(kc_) * rs;
+      const RowCols<T, D> kr(kp + base + static_cast<size_t>(kc_) * rs, h);
       float* dst = dqx + wave * kScratch + (c >> lw) * D;
       with_lw(lw, [&](auto LC) __attribute__((always_inline)) {
         constexpr int LW = decltype(LC)::value;
@@ -782,11 +866,12 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
 #pragma unroll
           for (int vq = 0; vq < Ge::NV / 4; ++vq) {
             const int d = 32 * dt + 8 * vq + 4 * h;
-            const Raw4<T> y = ld4(kr + d);
+            float y[4];
+            kr.get(dt, vq, y);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const float x =
-                  seg_reduce<LW>(rowvalid ? (y.at(e) + s.kp_bias) * aq[dt][4 * vq + e] : 0.f, OpSum());
+                  seg_reduce<LW>(rowvalid ? (y[e] + s.kp_bias) * aq[dt][4 * vq + e] : 0.f, OpSum());
               if ((c & ((1 << LW) - 1)) == 0) dst[d + e] = x;
             }
           }
@@ -797,8 +882,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
     // Phase ph: slot adds column tiles dt (head_dim 128), or quarters / halves of
     // them, whose number is (slot + ph) % QS.
     const int row = max(kk + WT, 0) % RB;
-    const T* qr = q + base + static_cast<size_t>(ic) * rs;
-    const T* gr = dout + base + static_cast<size_t>(ic) * rs;
+    const RowCols<T, D> qr(q + base + static_cast<size_t>(ic) * rs, h), gr(dout + base + static_cast<size_t>(ic) * rs, h);
     for (int ph = 0; ph < QS; ++ph) {
       const int sl = (slot + ph) & (QS - 1);
       for (int st = 0; st < SP; ++st) {  // a k-row belongs to one lane per query
@@ -809,14 +893,16 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
             for (int vq = 0; vq < Ge::NV / 4; ++vq) {
               if (((NDT * vq + dt) & (QS - 1)) != sl) continue;
               const int d = 32 * dt + 8 * vq + 4 * h;
-              const Raw4<T> x = ld4(qr + d), y = ld4(gr + d);
+              float x[4], y[4];
+              qr.get(dt, vq, x);
+              gr.get(dt, vq, y);
               float4* a = reinterpret_cast<float4*>(ring_k + row * RS + d);
               float4* z = reinterpret_cast<float4*>(ring_v + row * RS + d);
               float4 av = *a, zv = *z;
-              av.x += x.at(0) * aq[dt][4 * vq], av.y += x.at(1) * aq[dt][4 * vq + 1];
-              av.z += x.at(2) * aq[dt][4 * vq + 2], av.w += x.at(3) * aq[dt][4 * vq + 3];
-              zv.x += y.at(0) * au[dt][4 * vq], zv.y += y.at(1) * au[dt][4 * vq + 1];
-              zv.z += y.at(2) * au[dt][4 * vq + 2], zv.w += y.at(3) * au[dt][4 * vq + 3];
+              av.x += x[0] * aq[dt][4 * vq], av.y += x[1] * aq[dt][4 * vq + 1];
+              av.z += x[2] * aq[dt][4 * vq + 2], av.w += x[3] * aq[dt][4 * vq + 3];
+              zv.x += y[0] * au[dt][4 * vq], zv.y += y[1] * au[dt][4 * vq + 1];
+              zv.z += y[2] * au[dt][4 * vq + 2], zv.w += y[3] * au[dt][4 * vq + 3];
               *a = av;
               *z = zv;
             }
@@ -830,7 +916,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
       const int qi = x / D, d = x % D;
       if (ib + qi < ce) {
         float sum = 0.f;
-        for (int gg = 0; gg < groups; ++gg) sum += dqx[((qi / SP) * groups + gg) * kScratch + (qi % SP) * D + d];
+        for (int gg = 0; gg < groups; ++gg) sum += dqx[((qi / SP) * groups + gg) * kScratch + (qi % SP) * D + place<T, D>(d)];
         st1(dq + base + static_cast<size_t>(ib + qi) * rs + d, sum * s.scale);
       }
     }
@@ -900,6 +986,7 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
     const float* __restrict__ lse, const float* __restrict__ delta, T* __restrict__ dk, T* __restrict__ dv,
     float* __restrict__ part) {
   using Ge = Geo<D>;
+  using W = typename Wide<T, D>::W;
   constexpr int NDT = Ge::NDT, RS = D + 4, KW = key_waves<D>();
   // K and V operands, then masked_tile scratch; at the end the wavefronts' sums.
   constexpr int kPer = kSplit<T> ? 2 : 1;  // float4s of an operand in 16 bytes
@@ -1018,25 +1105,25 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
     }
     // Transposed operands: rows acc_row(v, h) of q / dO (their query's) and of
     // k' / v' (zero rows outside the sequence).
-    auto load_q = [&](__amdgpu_buffer_rsrc_t bb, int dt, T* r) {
+    auto load_q = [&](__amdgpu_buffer_rsrc_t bb, int dt, W* r) __attribute__((always_inline)) {
+      if (kWide<T, D> && dt > 0) return;
       int off = tr_col<T, D>(c);
       asm volatile("" : "+v"(off));
 #pragma unroll
       for (int vq = 0; vq < 4; ++vq)  // eight rows share a query
-        r[vq] = ldb1<T>(bb, off + ((8 * vq) >> lw) * rsb + 32 * dt * static_cast<int>(sizeof(T)));
+        r[vq] = ldw<T, D>(bb, off + ((8 * vq) >> lw) * rsb + 32 * dt * static_cast<int>(sizeof(T)));
     };
-    auto load_k = [&](__amdgpu_buffer_rsrc_t bb, int dt) {
-      TrChunk<T> r;
+    auto load_k = [&](__amdgpu_buffer_rsrc_t bb, int dt, TrChunk<T, D>& r) __attribute__((always_inline)) {
+      if (kWide<T, D> && dt > 0) return;
       int off = tr_col<T, D>(c) - 4 * h * rsb;
       asm volatile("" : "+v"(off));  // the sixteen offsets are formed here, not kept in registers
 #pragma unroll
       for (int v = 0; v < 16; ++v)
-        r.x[v] = ldb1<T>(bb, off + (i0 - k0 + ((8 * (v >> 2)) >> lw) - tq[v >> 2] - (v & 3)) * rsb +
-                                 32 * dt * static_cast<int>(sizeof(T)));
-      return r;
+        r.x[v] = ldw<T, D>(bb, off + (i0 - k0 + ((8 * (v >> 2)) >> lw) - tq[v >> 2] - (v & 3)) * rsb +
+                                   32 * dt * static_cast<int>(sizeof(T)));
     };
-    T ta[4];
-    TrChunk<T> tm;
+    W ta[4];
+    TrChunk<T, D> tm;
 #pragma unroll
     for (int ch = 0; ch < Ge::NRC; ++ch) {
       RowChunk<T, D> na, nm;
@@ -1045,7 +1132,7 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
         nm = load_rows<T, D>(bvp, ko, ch + 1);
       } else {
         load_q(bg, 0, ta);
-        tm = load_k(bvp, 0);
+        load_k(bvp, 0, tm);
       }
       float x[4 * Ge::RC];
 #pragma unroll
@@ -1098,18 +1185,18 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
 #pragma unroll
     for (int x = 0; x < 2 * NDT; ++x) {
       const int dt = x % NDT;
-      const T ca[4] = {ta[0], ta[1], ta[2], ta[3]};
-      const TrChunk<T> cm = tm;
+      const W ca[4] = {ta[0], ta[1], ta[2], ta[3]};
+      const TrChunk<T, D> cm = tm;
       if (x + 1 < 2 * NDT) {
         load_q(x + 1 < NDT ? bg : bq, (x + 1) % NDT, ta);
-        tm = load_k(x + 1 < NDT ? bvp : bkp, (x + 1) % NDT);
+        load_k(x + 1 < NDT ? bvp : bkp, (x + 1) % NDT, tm);
       }
       const float bias = x < NDT ? s.vp_bias : s.kp_bias;
       f32x16_t u = {};
       float y[16];
 #pragma unroll
       for (int vv = 0; vv < 16; ++vv) {
-        y[vv] = to_f32(ca[vv >> 2]) * plus_bias<BIAS>(to_f32(cm.x[vv]), bias);
+        y[vv] = elem<T, D>(ca[vv >> 2], dt) * plus_bias<BIAS>(elem<T, D>(cm.x[vv], dt), bias);
         if (D < 32) y[vv] = c < D ? y[vv] : 0.f;
       }
       if constexpr (split) {
@@ -1125,11 +1212,11 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
       }
       if (!split && edge && any_nonfinite(u))
         u = masked_tile<D>(x < NDT ? p : ds, lds + kOps + wave * kScratch, c, h, seen, [&](int r, int d, float* z) {
-          const int at = (32 * dt + d) * static_cast<int>(sizeof(T));
-          const Raw4<T> y0 = ldb4<T>(x < NDT ? bg : bq, (r >> lw) * rsb + at);
-          const Raw4<T> y1 = ldb4<T>(x < NDT ? bvp : bkp, (i0 - k0 + (r >> lw) - tof(r)) * rsb + at);
+          float y1[4];
+          ldcols<T, D>(x < NDT ? bg : bq, (r >> lw) * rsb, dt, d, z);
+          ldcols<T, D>(x < NDT ? bvp : bkp, (i0 - k0 + (r >> lw) - tof(r)) * rsb, dt, d, y1);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) z[e] = y0.at(e) * plus_bias<BIAS>(y1.at(e), bias);
+          for (int e = 0; e < 4; ++e) z[e] *= plus_bias<BIAS>(y1[e], bias);
         });
       if (x < NDT)
         av[dt] += u;
@@ -1159,7 +1246,7 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
       if (j0 + r >= N) continue;
       float sum = 0.f;
 #pragma unroll
-      for (int w = 0; w < KW; ++w) sum += lds[(w * 32 + r) * RS + d];
+      for (int w = 0; w < KW; ++w) sum += lds[(w * 32 + r) * RS + place<T, D>(d)];
       if (ks > 1)
         part[((static_cast<size_t>(sp) * 2 + pass) * s.B * s.H * N + stat + j0 + r) * D + d] = sum;
       else
