@@ -258,11 +258,10 @@ __global__ __launch_bounds__(64 * WAVES) void bwd_q_kernel(
   // (16 bytes per lane per load, the chunk that belongs at LDS offset
   // 1024 k + 16 lane of the swizzled tile); stage_put writes it into a stage
   // one block later.
-  // A tile's key window union starts at max(0, i0 - w1 + 1): the first tiles of
-  // a head walk only the blocks that hold keys.
+  // The first tiles of a head leave out the blocks before the sequence.
   const int ntiles = (ce - cs + QW - 1) / QW;
-  auto tile_jlo = [&](int i0) { return max(i0 - w1 + 1, 0); };
-  auto tile_nb = [&](int i0) { return (i0 + QW - 1 - tile_jlo(i0) + 32) / 32; };
+  auto tile_jlo = [&](int i0) { return i0 - w1 + 1 + 32 * blocks_before_start(i0 - w1 + 1); };
+  auto tile_nb = [&](int i0) { return (w1 + QW - 1 + 31) / 32 - blocks_before_start(i0 - w1 + 1); };
   int total_it = ntiles * tile_nb(cs);
   if (cs < w1 - 1) {
     total_it = 0;
@@ -409,7 +408,7 @@ __global__ __launch_bounds__(64 * WAVES) void bwd_q_kernel(
       const char* kt = smem + S * L::stageBytes;
       const char* vt = kt + T::bytes;
       // Keys of this block inside query i's window and inside [0, N).
-      const int lo = max(i - w1 + 1 - jlo, 0) - 32 * blk;
+      const int lo = max(i - w1 + 1, 0) - jlo - 32 * blk;
       const int hi = min(i, N - 1) - jlo - 32 * blk;
       const bool edge = lo > 0 || hi < 31;
 

@@ -210,11 +210,10 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
   // Wavefronts w < F::instrs move the K and V tiles of a block, 16 bytes per
   // lane, into the fragment-major layout; block `it` goes into stage it % NS.
   using F = FragTile<D>;
-  // A tile's key window union starts at max(0, i0 - w1 + 1): the first tiles of
-  // a head walk only the blocks that hold keys.
+  // The first tiles of a head leave out the blocks before the sequence.
   const int ntiles = (ce - cs + QW - 1) / QW;
-  auto tile_jlo = [&](int i0) { return max(i0 - w1 + 1, 0); };
-  auto tile_nb = [&](int i0) { return (i0 + QW - 1 - tile_jlo(i0) + 32) / 32; };
+  auto tile_jlo = [&](int i0) { return i0 - w1 + 1 + 32 * blocks_before_start(i0 - w1 + 1); };
+  auto tile_nb = [&](int i0) { return (w1 + QW - 1 + 31) / 32 - blocks_before_start(i0 - w1 + 1); };
   const __amdgpu_buffer_rsrc_t rk = make_rsrc(k + basek, hbk), rv = make_rsrc(v + basek, hbk);
   const bool stager = wave < F::instrs;
   const int st_row = (64 * wave + lane) / F::CH, st_ch = (64 * wave + lane) % F::CH;
@@ -399,7 +398,7 @@ __global__ __launch_bounds__(kQThreads, 1) void bwd_query_kernel(
         f32x16_t sacc = mfma32(ka[0], qt[0], f32x16_t{});
 #pragma unroll
         for (int t = 1; t < NT; ++t) sacc = mfma32(ka[t], qt[t], sacc);
-        const int lo = max(i - w1 + 1 - jlo, 0) - 32 * blk;
+        const int lo = max(i - w1 + 1, 0) - jlo - 32 * blk;
         const int hi = min(i, N - 1) - jlo - 32 * blk;
         float pr[16];
 #pragma unroll

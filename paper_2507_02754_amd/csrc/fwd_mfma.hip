@@ -165,11 +165,12 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_mfma_kernel(Shape s, const ui
   const bool rowvalid = qvalid && kk >= 0 && kk > i - w2;
   const float qscale = s.scale * kLog2e;
 
-  // Key window union of the tile, clipped at the start of the sequence: the
+  // Key window union of the tile, less the blocks before the sequence: the
   // first w1 queries of a head walk only the blocks that hold keys (a sequence
-  // no longer than w1 half of them).
-  const int jlo = max(i0 - w1 + 1, 0);
-  const int nb = (i0 + (HF ? 0 : QW - 1) - jlo + 32) / 32;
+  // no longer than w1 about half of them).
+  const int skip = blocks_before_start(i0 - w1 + 1);
+  const int jlo = i0 - w1 + 1 + 32 * skip;
+  const int nb = (w1 + (HF ? 0 : QW - 1) + 31) / 32 - skip;
   const int rsbq = static_cast<int>(rs) * 2;     // bytes between rows of q, out
   const int rsb = static_cast<int>(rskv) * 2;    // bytes between rows of k, k', v, v'
   const __amdgpu_buffer_rsrc_t rk = make_rsrc(k + kvbase, head_bytes(N, rsb, D));
@@ -224,12 +225,12 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_mfma_kernel(Shape s, const ui
     lrow[x] = p / T::CH;
     lcol[x] = 16 * ((p % T::CH) ^ T::swz(lrow[x]));
   }
-  // Tiles whose blocks all lie inside the sequence (all but the last few of
-  // each head) skip the per-block bounds test.
-  const bool interior = jlo + 32 * nb <= N;
+  // Tiles whose blocks all lie inside the sequence (all but those of the first
+  // w1 queries and the last few of each head) skip the per-block bounds test.
+  const bool interior = jlo >= 0 && jlo + 32 * nb <= N;
   auto load_tile = [&](__amdgpu_buffer_rsrc_t r, lds_char* dst, int blk) __attribute__((always_inline)) {
     const int jb = jlo + 32 * blk;
-    if (interior || jb + 31 < N) {
+    if (interior || (jb >= 0 && jb + 31 < N)) {
       // Block inside the sequence: the block's row offset goes in the
       // scalar offset, the lane's offset within the block is fixed.
 #pragma unroll
@@ -242,7 +243,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_mfma_kernel(Shape s, const ui
 #pragma unroll
       for (int x = 0; x < SPW; ++x) {
         const int kx = x * kWaves + wave;
-        const int row = min(jb + lrow[x], N - 1);
+        const int row = min(max(jb + lrow[x], 0), N - 1);
         if (T::instrs % kWaves == 0 || kx < T::instrs) load_lds16(r, dst + 1024 * kx, row * rsb + lcol[x]);
       }
     }
@@ -445,7 +446,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_mfma_kernel(Shape s, const ui
       for (int dt = 0; dt < NDT; ++dt) vf[u][dt] = vfrag(SC, dt, u);
 
     // Valid block-local columns of this wavefront's query.
-    const int lo = max(i - w1 + 1 - jlo, 0) - 32 * blk;
+    const int lo = max(i - w1 + 1, 0) - jlo - 32 * blk;
     const int hi = min(i, N - 1) - jlo - 32 * blk;
     if (lo > 0 || hi < 31) {
 #pragma unroll

@@ -135,6 +135,13 @@ __device__ __forceinline__ void cross8_t(const float* x, const float* y, int t, 
     out[e] = h == 0 ? v0 : v1;
   }
 }
+// Key blocks (32 keys) of a tile whose key window starts at jfull that lie
+// wholly before the sequence. The kernels skip them and keep the other blocks
+// where they are: every sum and running maximum is what it is with the blocks
+// walked and masked, and a tile reads no later key than it otherwise would
+// (starting at key 0 instead moves the last block up to 31 keys past the
+// tile's own, whose V rows then enter as 0 * V, NaN where V is not finite).
+__device__ __forceinline__ int blocks_before_start(int jfull) { return max(-jfull, 0) >> 5; }
 // Byte-range of one head's rows of a [.., N, H, D] bf16 tensor, from row 0 to
 // the end of row N-1 (rows are rs_bytes apart).
 __device__ __forceinline__ unsigned head_bytes(int N, int rs_bytes, int D) {
