@@ -158,7 +158,8 @@ int forward(const void* q, const void* k, const void* kp, const void* v, const v
   s.vp_bias = vp_bias;
   hipStream_t st = static_cast<hipStream_t>(stream);
   switch (choose_path(0, B, N, H, D, w1, w2, dtype)) {
-    case Path::Generic: return to_status(sa::f32_fwd(s, q, k, kp, v, vp, out, lse, st));
+    case Path::Generic:
+      return to_status((sa::f32_fwd_supported(s) ? sa::f32_fwd : sa::generic_fwd)(s, q, k, kp, v, vp, out, lse, st));
     case Path::Mfma: return to_status(sa::mfma_fwd(s, q, k, kp, v, vp, out, lse, st));
     default: return SA_ERR_UNSUPPORTED;
   }
@@ -176,10 +177,11 @@ int run_stage(const Shape& s, Path path, BwdStage stage, const void* q, const vo
   if (path == Path::Mfma)
     return to_status(
         sa::mfma_bwd_stage(s, stage, q, k, kp, v, vp, dout, lse, g0, g1, g2, workspace, st));
-  // Trilinear logits take the float32 MFMA kernels; determinant logits and the
-  // query side of w2 > 128 (whose k-rows overflow the LDS ring) the plain ones.
+  // Trilinear logits take the float32 MFMA kernels; determinant logits, the
+  // query side of w2 > 128 (whose k-rows overflow the LDS ring) and strides past
+  // 32-bit offsets the plain ones.
   const float* delta = static_cast<const float*>(workspace);
-  if (s.form == 0 && (stage == BwdStage::Key || sa::f32_bwd_query_supported(s))) {
+  if (stage == BwdStage::Key ? sa::f32_bwd_key_supported(s) : sa::f32_bwd_query_supported(s)) {
     float* halo = reinterpret_cast<float*>(static_cast<char*>(workspace) + sa::f32_bwd_plan(s).halo_off);
     return to_status(sa::f32_bwd_stage(s, stage, q, k, kp, v, vp, dout, lse, delta, g0, g1, g2, halo, st));
   }

@@ -41,6 +41,7 @@
 // that only some of the pairs of a block may see is then multiplied by 0 for
 // the others, which is not 0 if it holds infinities or NaN: such blocks add
 // their products term by term with the masked ones left out (masked_tile).
+#include "f32_offsets.h"
 #include "mfma_common.h"
 
 namespace sa {
@@ -91,8 +92,9 @@ __device__ __forceinline__ float to_f32(uint16_t x) { return bf16_to_f32(x); }
 // Rows n0 .. N - 1 of one head (row stride `rsb` bytes) as a buffer: loads take
 // a 32-bit byte offset from row n0 and rows past the sequence, or before n0
 // (negative offsets), load as zeros. A head may span more than 2^31 bytes: the
-// buffer starts at the block's own row and reaches as far as offsets do.
-constexpr int kFar = 0x7ffff000;  // an offset past every buffer's end
+// buffer starts at the block's own row and reaches as far as offsets do
+// (f32_offsets.h: shapes whose blocks span more do not come here).
+constexpr int kFar = static_cast<int>(f32_offsets::kReach);  // an offset past every buffer's end
 template <typename T, int D>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_from(const T* head, int n0, int N, size_t rsb) {
   const size_t left = n0 < N ? static_cast<size_t>(N - 1 - n0) * rsb + D * sizeof(T) : 0;
@@ -1274,8 +1276,12 @@ __global__ __launch_bounds__(256) void key_sum_f32_kernel(Shape s, int ks, const
   st1(dv + dst, y);
 }
 
-// log2 of the k-rows a wavefront gives each query: 8, 16 or 32 of its 32 rows.
-int row_bits(int w2) { return w2 <= 8 ? 3 : w2 <= 16 ? 4 : 5; }
+using f32_offsets::row_bits;
+
+// Whether the row offsets of a tensor of `heads` heads fit the kernels' buffers.
+bool rows_fit(const Shape& s, int rows, int heads) {
+  return f32_offsets::fits(rows, static_cast<long long>(heads) * s.D * (s.dtype == 0 ? 4 : 2));
+}
 
 template <typename T, int D>
 hipError_t fwd_go(const Shape& s, const void* q, const void* k, const void* kp, const void* v, const void* vp,
@@ -1329,8 +1335,16 @@ hipError_t bwd_go(const Shape& s, BwdStage stage, const void* q_, const void* k_
 
 }  // namespace
 
+bool f32_fwd_supported(const Shape& s) {
+  return s.form == 0 && rows_fit(s, f32_offsets::kBlockRows, s.Hkv);  // q is indexed in 64 bits
+}
+bool f32_bwd_key_supported(const Shape& s) {
+  return s.form == 0 && s.Hkv == s.H && rows_fit(s, f32_offsets::kBlockRows, s.H);
+}
 // The query side's ring holds 128 k-rows in LDS; longer w2 take the plain kernels.
-bool f32_bwd_query_supported(const Shape& s) { return s.form == 0 && s.w2 <= 128 && s.Hkv == s.H; }
+bool f32_bwd_query_supported(const Shape& s) {
+  return s.form == 0 && s.w2 <= 128 && s.Hkv == s.H && rows_fit(s, f32_offsets::query_rows(s.w2), s.H);
+}
 
 F32Plan f32_bwd_plan(const Shape& s) {
   F32Plan p{};
@@ -1367,7 +1381,9 @@ F32Plan f32_bwd_plan(const Shape& s) {
   // Key side: a key block's row blocks go to up to four workgroups while there
   // are too few key blocks for the CUs (the sum costs a launch: 5 us).
   const size_t n = bh * static_cast<size_t>(s.N) * s.D;
-  while (p.ks < 4 && bh * ((s.N + 31) / 32) * p.ks < 192 && fits(p.key_floats + 4 * p.ks * n)) p.ks *= 2;
+  while (f32_bwd_key_supported(s) && p.ks < 4 && bh * ((s.N + 31) / 32) * p.ks < 192 &&
+         fits(p.key_floats + 4 * p.ks * n))
+    p.ks *= 2;
   p.bytes += 4 * (p.key_floats + (p.ks > 1 ? 2 * p.ks * n : 0));
   return p;
 }

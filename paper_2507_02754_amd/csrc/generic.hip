@@ -1,7 +1,8 @@
-// Plain kernels, written for clarity rather than speed: the determinant logits
-// outside the bf16 kernels' shapes, and the trilinear query-side gradients with
-// w2 > 128 (the other float32 and small shapes run in f32.hip). Also Delta for
-// all of them.
+// Plain kernels, written for clarity rather than speed, for every dtype, head_dim,
+// window pair and stride: the determinant logits outside the bf16 kernels'
+// shapes, and of the trilinear ones the query-side gradients with w2 > 128 and
+// row strides past the 32-bit offsets of f32.hip (which runs the other float32
+// and small shapes). Also Delta for all of them.
 //
 // One workgroup of 256 threads owns one output row. Threads stride over the
 // (j, k) pairs of that row, each keeping a private D-vector accumulator in
@@ -346,15 +347,22 @@ __global__ __launch_bounds__(kThreads) void keyside_kernel(
   if (threadIdx.x < D) st(grad + rows.at(r) + threadIdx.x, MODE == 0 ? g * s.scale : g);
 }
 
-template <typename T, int D>
-hipError_t fwd_t(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
+template <typename T, int D, int FORM>
+hipError_t fwd_f(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
                  const void* vp, void* out, float* lse, hipStream_t st) {
   const unsigned grid = static_cast<unsigned>(s.N) * s.B * s.H;
-  hipLaunchKernelGGL((fwd_kernel<T, D, 1>), dim3(grid), dim3(kThreads), 0, st, s,
+  hipLaunchKernelGGL((fwd_kernel<T, D, FORM>), dim3(grid), dim3(kThreads), 0, st, s,
                      static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(kp),
                      static_cast<const T*>(v), static_cast<const T*>(vp), static_cast<T*>(out),
                      lse);
   return hipGetLastError();
+}
+
+template <typename T, int D>
+hipError_t fwd_t(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
+                 const void* vp, void* out, float* lse, hipStream_t st) {
+  return s.form == 0 ? fwd_f<T, D, 0>(s, q, k, kp, v, vp, out, lse, st)
+                     : fwd_f<T, D, 1>(s, q, k, kp, v, vp, out, lse, st);
 }
 
 template <typename T, int D, int FORM>
@@ -369,13 +377,11 @@ hipError_t bwd_stage_f(const Shape& s, BwdStage stage, const T* q, const T* k, c
                        kp, k, vp, v, dout, lse, delta, static_cast<T*>(g1));
     hipLaunchKernelGGL((keyside_kernel<T, D, 1, 1, FORM>), dim3(grid), dim3(kThreads), 0, st, s, q,
                        kp, k, vp, v, dout, lse, delta, static_cast<T*>(g2));
-  } else if constexpr (FORM == 1) {
+  } else {
     hipLaunchKernelGGL((keyside_kernel<T, D, 0, 0, FORM>), dim3(grid), dim3(kThreads), 0, st, s, q,
                        k, kp, v, vp, dout, lse, delta, static_cast<T*>(g0));
     hipLaunchKernelGGL((keyside_kernel<T, D, 0, 1, FORM>), dim3(grid), dim3(kThreads), 0, st, s, q,
                        k, kp, v, vp, dout, lse, delta, static_cast<T*>(g1));
-  } else {
-    return hipErrorInvalidValue;  // the trilinear key side is f32.hip's for every shape
   }
   return hipGetLastError();
 }
@@ -406,7 +412,6 @@ hipError_t bwd_stage_t(const Shape& s, BwdStage stage, const void* q_, const voi
     default: return hipErrorInvalidValue;     \
   }
 
-// Determinant logits only.
 hipError_t generic_fwd(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
                        const void* vp, void* out, float* lse, hipStream_t st) {
   if (s.dtype == 0) {

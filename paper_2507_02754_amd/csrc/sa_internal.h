@@ -48,8 +48,7 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
   return static_cast<uint16_t>(u >> 16);
 }
 
-// ---- plain kernels (generic.hip): determinant logits of any dtype, head_dim and
-// windows; of the trilinear backward the query side ----
+// ---- plain kernels (generic.hip): any dtype, head_dim, windows and strides ----
 hipError_t generic_fwd(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
                        const void* vp, void* out, float* lse, hipStream_t st);
 // The backward is split into a query-side stage (dQ, dK', dV') and a key-side
@@ -61,6 +60,10 @@ hipError_t generic_bwd_stage(const Shape& s, BwdStage stage, const void* q, cons
                              hipStream_t st);
 
 // ---- float32 arithmetic on the matrix cores (f32.hip; trilinear logits) ----
+// Whether its kernels take the shape (the plain ones take every one).
+bool f32_fwd_supported(const Shape& s);
+bool f32_bwd_query_supported(const Shape& s);
+bool f32_bwd_key_supported(const Shape& s);
 hipError_t f32_fwd(const Shape& s, const void* q, const void* k, const void* kp, const void* v,
                    const void* vp, void* out, float* lse, hipStream_t st);
 // Work split of its backward and workspace: Delta ([B, H, N] floats), then from
@@ -74,8 +77,6 @@ struct F32Plan {
   size_t halo_floats, key_floats, halo_off, bytes;
 };
 F32Plan f32_bwd_plan(const Shape& s);
-// Whether its query side takes the shape (its key side takes every one).
-bool f32_bwd_query_supported(const Shape& s);
 hipError_t f32_bwd_stage(const Shape& s, BwdStage stage, const void* q, const void* k,
                          const void* kp, const void* v, const void* vp, const void* dout,
                          const float* lse, const float* delta, void* g0, void* g1, void* g2,

@@ -148,3 +148,26 @@ def test_bf16_products_in_parts_equal_float32(d, w2, n, bad):
         # bf16 rounding plus float32 sums of the size of the largest
         bound = 4e-6 * max(big, 1.0) if t == 1 else 2.0 ** -8 * r[ok].abs() + 4e-6 * big
         assert bool((err <= bound).all()), (t, float(err.max()))
+
+
+@pytest.mark.parametrize("h,n,w1,w2", [
+    (33026, 129, 3, 128),   # 128 k-rows span more than 2^31 bytes: query side
+    (105000, 41, 41, 5),    # so do 32 keys: forward and both sides
+])
+def test_f32_strides_past_32_bit_offsets(h, n, w1, w2):
+    """Many heads: rows of one head lie so far apart that those of a block span
+    more than a 32-bit offset. First, middle and last head against the oracle."""
+    d, scale = 128, 128 ** -0.5
+    print(f"\n[f32] strides H={h} N={n} w2={w2}", flush=True)
+    assert n * h * d * 4 > 1 << 31
+    g = torch.Generator(device="cuda").manual_seed(h)
+    x = [torch.randn((1, n, h, d), generator=g, device="cuda") for _ in range(6)]
+    o, lse = simplicial_attn_fwd(*x[:5], w1, w2, scale)
+    grads = simplicial_attn_bwd(*x[:5], o, x[5], lse, w1, w2, scale)
+    torch.cuda.synchronize()
+    for head in (0, h // 2, h - 1):
+        one = [t[:, :, head:head + 1].cpu() for t in x]
+        o_ref, lse_ref, g_ref = P.full_oracle(one, w1, w2, scale)
+        P.check_forward(P.to64(o[:, :, head:head + 1]), P.to64(lse[:, head:head + 1]), o_ref, lse_ref, "fp32",
+                        f"head {head}")
+        P.check_grads([P.to64(t[:, :, head:head + 1]) for t in grads], g_ref, "fp32", f"head {head}")
