@@ -35,7 +35,11 @@
 // for accumulator tile dt lane (h, c) reads column 32 dt + c of that row.
 //
 // Every block's products start from zero and are added to the running sums
-// afterwards: sums over thousands of rows then round once per 32 of them.
+// afterwards: sums over thousands of rows then round once per 32 of them. The
+// float32 products of a logit run in two chains of D / 2 columns added at the
+// end: the rounding of one chain of D is the largest error of every output (D =
+// 64: 2.0e-7 of O, the products' operands 0.3e-7; two chains 1.3e-7). The second
+// chain takes the registers of dP (or of the products with V), free at that point.
 //
 // Masked pairs: their probabilities are set to 0. A row of V (or K, dO, ...)
 // that only some of the pairs of a block may see is then multiplied by 0 for
@@ -479,7 +483,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
     RowChunk<T, D> kc = load_rows<T, D>(bk, roff, 0);
     for (int jb = jlo; jb <= jhi; jb += 32) {
       const __amdgpu_buffer_rsrc_t bv = rows_from<T, D>(vb, jb, N, rsb);
-      f32x16_t sc = {};
+      f32x16_t sc = {}, sc2 = {};
       TrChunk<T, D> vc;
 #pragma unroll
       for (int ch = 0; ch < Ge::NRC; ++ch) {
@@ -495,11 +499,15 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void fwd_f32_kernel(
 #pragma unroll
           for (int t = 0; t < Ge::RC; ++t)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sc = mfma_f32(kc.x[t].at(e), qt[4 * (ch * Ge::RC + t) + e], sc);
+            for (int e = 0; e < 4; ++e) {
+              f32x16_t& chain = t & 1 ? sc2 : sc;
+              chain = mfma_f32(kc.x[t].at(e), qt[4 * (ch * Ge::RC + t) + e], chain);
+            }
         }
         kc = nx;
         __builtin_amdgcn_sched_barrier(0);
       }
+      if constexpr (!split) sc += sc2;
       // Online softmax over this block's 32 keys (16 in each lane half).
       float p[16], mx = -INFINITY;
 #pragma unroll
@@ -782,8 +790,8 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
                 fm = load_rows<T, D>(second ? bvp : bkp, ko, nch);
               }
             }
-            f32x16_t& acc = ph ? dp : sc;
             if constexpr (split) {
+              f32x16_t& acc = ph ? dp : sc;
 #pragma unroll
               for (int u = 0; u < Ge::RC / 2; ++u)
                 acc = ph ? mfma_parts(frag<T, D>(cur, u), op[ch * Ge::RC / 2 + u], acc)
@@ -792,9 +800,16 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
 #pragma unroll
               for (int t = 0; t < Ge::RC; ++t)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc = mfma_f32(cur.x[t].at(e), y[4 * t + e], acc);
+                for (int e = 0; e < 4; ++e) {
+                  f32x16_t& acc = ph || (t & 1) ? dp : sc;  // S: its second chain
+                  acc = mfma_f32(cur.x[t].at(e), y[4 * t + e], acc);
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
+          }
+          if (!split && ph == 0) {
+            sc += dp;
+            dp = f32x16_t{};
           }
         }
         float p[16], ds[16];
@@ -1098,12 +1113,19 @@ __global__ __launch_bounds__(64 * key_waves<D>(), 1) void bwd_key_f32_kernel(
         for (int t = 0; t < Ge::RC; ++t) {
           const u32x4_t w = opk[64 * ((ch * Ge::RC + t) / kPer)];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) sc = mfma_f32(x[4 * t + e], op_at(w, t, e), sc);
+          for (int e = 0; e < 4; ++e) {
+            f32x16_t& chain = t & 1 ? dp : sc;
+            chain = mfma_f32(x[4 * t + e], op_at(w, t, e), chain);
+          }
         }
       }
       a = na;
       m = nm;
       __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (!split) {
+      sc += dp;
+      dp = f32x16_t{};
     }
     // Transposed operands: rows acc_row(v, h) of q / dO (their query's) and of
     // k' / v' (zero rows outside the sequence).

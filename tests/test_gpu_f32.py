@@ -171,3 +171,24 @@ def test_f32_strides_past_32_bit_offsets(h, n, w1, w2):
         P.check_forward(P.to64(o[:, :, head:head + 1]), P.to64(lse[:, head:head + 1]), o_ref, lse_ref, "fp32",
                         f"head {head}")
         P.check_grads([P.to64(t[:, :, head:head + 1]) for t in grads], g_ref, "fp32", f"head {head}")
+
+
+def test_f32_logits_in_two_chains():
+    """The rounding of a logit's running sum is the largest error of the float32
+    forward. One chain of D products of rms t carries u t D / sqrt(6) of it (u =
+    2^-24), two chains of D / 2 and their sum sqrt(1/2 + 2/D) = 0.73 of that; the
+    operands' rounding adds 2%. Emulated on the CPU with everything else exact,
+    O at this shape is 1.9e-7 off with one chain and 1.3e-7 with two. With the
+    kernel's other roundings 2.31e-7 and 1.62e-7: the bound lies between."""
+    n, h, d, w1, w2 = 400, 4, 64, 256, 16
+    err = ref = 0.0
+    for seed in range(2):
+        inputs = draw((1, n, h, d), seed=1000 + seed, dtype=torch.float32)
+        o, _ = simplicial_attn_fwd(*(t.cuda() for t in inputs[:5]), w1, w2, d ** -0.5)
+        o_ref = P.full_oracle(inputs, w1, w2, d ** -0.5)[0]
+        o = P.to64(o)
+        err += float(((o - o_ref) ** 2).sum())
+        ref += float((o_ref ** 2).sum())
+    rel = (err / ref) ** 0.5
+    print(f"\n[f32] O against float64: {rel:.3e}", flush=True)
+    assert rel <= 2.0e-7
