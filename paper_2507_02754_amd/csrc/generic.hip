@@ -216,26 +216,32 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(Shape s, const T* __restr
 }
 
 // ------------------------------------------------------------------ delta ---
-// D / 4 lanes per query row, four elements each.
+// D / 4 lanes per query row, four elements each; a workgroup takes every
+// gridDim.x-th run of rows (a launch holds fewer than 2^32 threads, and this one
+// would need rows * D / 4).
+constexpr unsigned kDeltaBlocks = 65536;
 template <typename T, int D>
 __global__ __launch_bounds__(kThreads) void delta_kernel(Shape s, const T* __restrict__ out,
                                                          const T* __restrict__ dout,
                                                          float* __restrict__ delta) {
   constexpr int LPR = D / 4;
-  const int64_t idx = (static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x) / LPR;
   const int part = threadIdx.x % LPR;
   const int64_t total = static_cast<int64_t>(s.B) * s.H * s.N;
-  float acc = 0.f;
-  if (idx < total) {
-    const int i = static_cast<int>(idx % s.N);
-    const int bh = static_cast<int>(idx / s.N);
-    const size_t off = ((static_cast<size_t>(bh / s.H) * s.N + i) * s.H + bh % s.H) * D + 4 * part;
+  for (int64_t row0 = static_cast<int64_t>(blockIdx.x) * (kThreads / LPR); row0 < total;
+       row0 += static_cast<int64_t>(gridDim.x) * (kThreads / LPR)) {
+    const int64_t idx = row0 + threadIdx.x / LPR;
+    float acc = 0.f;
+    if (idx < total) {
+      const int i = static_cast<int>(idx % s.N);
+      const int bh = static_cast<int>(idx / s.N);
+      const size_t off = ((static_cast<size_t>(bh / s.H) * s.N + i) * s.H + bh % s.H) * D + 4 * part;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc += ld(out + off + e) * ld(dout + off + e);
+      for (int e = 0; e < 4; ++e) acc += ld(out + off + e) * ld(dout + off + e);
+    }
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if (idx < total && part == 0) delta[idx] = acc;
   }
-#pragma unroll
-  for (int off = LPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  if (idx < total && part == 0) delta[idx] = acc;
 }
 
 // --------------------------------------------------------------------- dQ ---
@@ -422,8 +428,8 @@ hipError_t generic_fwd(const Shape& s, const void* q, const void* k, const void*
 
 template <typename T, int D>
 static hipError_t delta_go(const Shape& s, const void* out, const void* dout, float* delta, hipStream_t st) {
-  const int64_t threads = static_cast<int64_t>(s.B) * s.H * s.N * (D / 4);
-  hipLaunchKernelGGL((delta_kernel<T, D>), dim3(static_cast<unsigned>((threads + kThreads - 1) / kThreads)),
+  const int64_t blocks = (static_cast<int64_t>(s.B) * s.H * s.N * (D / 4) + kThreads - 1) / kThreads;
+  hipLaunchKernelGGL((delta_kernel<T, D>), dim3(blocks < kDeltaBlocks ? static_cast<unsigned>(blocks) : kDeltaBlocks),
                      dim3(kThreads), 0, st, s, static_cast<const T*>(out), static_cast<const T*>(dout), delta);
   return hipGetLastError();
 }

@@ -7,8 +7,8 @@ import torch
 
 import parity as P
 from paper_2507_02754_amd import (load_library, simplicial_attn_bwd, simplicial_attn_bwd_noalloc,
-                                  simplicial_attn_bwd_workspace_size, simplicial_attn_fwd,
-                                  simplicial_attn_path_name)
+                                  simplicial_attn_bwd_preprocess, simplicial_attn_bwd_workspace_size,
+                                  simplicial_attn_fwd, simplicial_attn_path_name)
 from paper_2507_02754_amd.workloads import draw
 
 pytestmark = pytest.mark.gpu
@@ -192,3 +192,38 @@ def test_f32_logits_in_two_chains():
     rel = (err / ref) ** 0.5
     print(f"\n[f32] O against float64: {rel:.3e}", flush=True)
     assert rel <= 2.0e-7
+
+
+@pytest.mark.parametrize("n,h,d,dt", [(4194304 + 77, 1, 16, "bf16"), (300001, 2, 128, "fp32"), (1, 1, 16, "fp32"),
+                                      (65, 3, 64, "fp32")])
+def test_f32_delta_of_many_rows(n, h, d, dt):
+    """Delta where its launch has fewer workgroups than runs of rows (more than
+    2^26 elements), and of few rows."""
+    dtype = torch.float32 if dt == "fp32" else torch.bfloat16
+    print(f"\n[f32] delta N={n} H={h} D={d} {dt}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    o, do = (torch.randn((1, n, h, d), generator=g, device="cuda").to(dtype) for _ in range(2))
+    ws = torch.empty(simplicial_attn_bwd_workspace_size(1, n, h, d, 1, 1, dtype), dtype=torch.uint8, device="cuda")
+    simplicial_attn_bwd_preprocess(o, do, 1, 1, ws)
+    delta = ws[:4 * n * h].view(torch.float32).view(h, n)
+    ref = (o.double() * do.double()).sum(-1)[0].t()
+    # D products and D - 1 sums, each 2^-24 of at most the sum of magnitudes
+    bound = d * 2.0 ** -24 * (o.double() * do.double()).abs().sum(-1)[0].t()
+    assert bool(((delta.double() - ref).abs() <= bound).all())
+
+
+def test_f32_delta_of_2_to_the_30_rows():
+    """Sizes whose Delta would take 2^32 threads at four elements each."""
+    n, d = (1 << 30) + 5, 16
+    print(f"\n[f32] delta N={n}", flush=True)
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 73 GB of GPU memory")
+    o, do = (torch.empty((1, n, 1, d), dtype=torch.bfloat16, device="cuda").fill_(x) for x in (0.5, 0.25))
+    rows = torch.tensor([0, 1, n // 2, n - 2, n - 1], device="cuda")
+    o[0, rows] = torch.arange(1, 6, dtype=torch.bfloat16, device="cuda").view(5, 1, 1)
+    ws = torch.empty(simplicial_attn_bwd_workspace_size(1, n, 1, d, 1, 1, o.dtype), dtype=torch.uint8, device="cuda")
+    simplicial_attn_bwd_preprocess(o, do, 1, 1, ws)
+    delta = ws[:4 * n].view(torch.float32)
+    assert delta[rows].tolist() == [4.0 * x for x in range(1, 6)]
+    delta[rows] = 2.0
+    assert float(delta.min()) == 2.0 and float(delta.max()) == 2.0
