@@ -50,7 +50,7 @@ extern "C" {
 #define SA_OK 0
 #define SA_ERR_INVALID 1     /* null pointer, non-positive size, w < 1, misaligned pointer, overflow */
 #define SA_ERR_UNSUPPORTED 2 /* head_dim or dtype this build does not implement */
-#define SA_ERR_WORKSPACE 3   /* workspace smaller than simplicial_attn_bwd_workspace_size() */
+#define SA_ERR_WORKSPACE 3   /* workspace too small (see simplicial_attn_bwd_workspace_size) */
 #define SA_ERR_HIP 4         /* HIP runtime reported an error when launching */
 #define SA_ERR_SCRATCH 5     /* simplicial_attn_bwd_noalloc: sizes need more than its fixed scratch */
 
@@ -90,9 +90,15 @@ int simplicial_attn_fwd_gqa(const void* q, const void* k, const void* kp, const 
                             int32_t dtype, void* stream);
 
 /*
- * Bytes of device workspace simplicial_attn_bwd needs for these sizes (the
+ * Bytes of device workspace simplicial_attn_bwd takes for these sizes (the
  * per-query Delta = <dO_i, O_i> and the partial sums the backward reduces
  * deterministically). Returns 0 for arguments simplicial_attn_bwd would reject.
+ * Few heads and queries are split over more workgroups, whose partial sums can
+ * make this larger than for a longer sequence. A workspace of another, longer
+ * sequence (the same other arguments) is accepted all the same: the work is
+ * split as far as the partial sums fit in what is passed (same gradients up to
+ * the order of fp32 additions; equal sizes give equal bits). The same holds for
+ * the other backward entry points with a workspace, except the fused ones.
  */
 size_t simplicial_attn_bwd_workspace_size(int64_t B, int64_t N, int64_t H, int64_t D, int32_t w1,
                                           int32_t w2, int32_t dtype);
@@ -104,8 +110,9 @@ size_t simplicial_attn_bwd_workspace_size(int64_t B, int64_t N, int64_t H, int64
  *   out, lse           forward outputs of the same call  [B, N, H, D] dtype / [B, H, N] f32
  *   dout               upstream gradient dO               [B, N, H, D], dtype
  *   dq, dk, dkp, dv, dvp  gradients, fully overwritten   [B, N, H, D], dtype
- *   workspace          device scratch of at least simplicial_attn_bwd_workspace_size()
- *                      bytes, 16-byte aligned; contents on entry are ignored
+ *   workspace          device scratch of simplicial_attn_bwd_workspace_size() bytes
+ *                      (there: smaller ones), 16-byte aligned; contents on entry
+ *                      are ignored
  *   other arguments    as simplicial_attn_fwd
  * The result is bitwise deterministic: no floating-point atomics are used.
  * It runs Section 7's two kernels (query side and key side; see the stage
@@ -155,10 +162,12 @@ int simplicial_attn_bwd_biased(const void* q, const void* k, const void* kp, con
  *          sums of the backward's deterministic reduction must fit the array.
  *          When the workspace simplicial_attn_bwd_workspace_size() reports
  *          fits, the kernels, their work split and the result are exactly
- *          those of simplicial_attn_bwd (bitwise). Otherwise the query-side
- *          kernel walks longer query chunks so that fewer partial sums are
- *          kept (same gradients up to the order of fp32 additions at chunk
- *          boundaries, still deterministic); sizes for which even that does
+ *          those of simplicial_attn_bwd (bitwise). Otherwise the work is split
+ *          as with a workspace of the array's size: the query-side kernel walks
+ *          longer query chunks and the key-side kernel shares a key block among
+ *          fewer workgroups, so that fewer partial sums are kept (same gradients
+ *          up to the order of fp32 additions, in dK', dV' at chunk boundaries
+ *          and in dK, dV, still deterministic); sizes for which even that does
  *          not fit return SA_ERR_SCRATCH, before any HIP call.
  *   Races  every call on one GPU uses that GPU's one array, and every call
  *          overwrites what it reads from it (contents on entry are ignored),
@@ -269,9 +278,11 @@ int simplicial_attn_bwd_key_side(const void* q, const void* k, const void* kp, c
  * as simplicial_attn_bwd up to the order of fp32 additions. Sequence on one
  * stream: simplicial_attn_bwd_preprocess (Delta), simplicial_attn_bwd_fused,
  * simplicial_attn_bwd_fused_reduce, all three with the same workspace of at
- * least simplicial_attn_bwd_fused_workspace_size() bytes: Delta plus
+ * least Delta (4 * B * H * N bytes, rounded up to 256) plus
  * 4 * B * H * ceil(N / 64) * ((63 + w1) + 2 * (94 + w1)) * D bytes of
  * partial sums (7.5 GB at B=1, H=16, N=32768, D=128, w1=512).
+ * simplicial_attn_bwd_fused_workspace_size() reports that, or
+ * simplicial_attn_bwd_workspace_size() where it is larger.
  * Shapes: bf16, head_dim 128, w2 <= 32; the size function returns 0 and the
  * two calls SA_ERR_UNSUPPORTED for others. kp_bias, vp_bias: the K' / V'
  * constants of simplicial_attn_bwd_biased (0 for the plain operation; the

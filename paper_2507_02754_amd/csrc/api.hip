@@ -75,13 +75,29 @@ Path choose_path(int which, int64_t B, int64_t N, int64_t H, int64_t D, int32_t 
 // Shapes the fused backward kernel takes.
 bool fused_path(const Shape& s) { return sa::mfma_fused_supported(s); }
 
+// Smallest workspace a backward stage runs with: the work is split as far as its
+// partial sums fit in what is passed. The size functions report the whole
+// split's, which is larger where there are few workgroups and so does not grow
+// with N everywhere (B=1 H=8 D=128 w1=512 w2=32: 16 MB at N=4096, 146 MB at
+// N=3000): a workspace of a longer sequence still serves a shorter one.
+size_t stage_min_bytes(const Shape& s) {
+  return sa::mfma_bwd_supported(s) ? sa::mfma_bwd_min_bytes(s) : sa::f32_bwd_plan(s).halo_off;
+}
+// Of a whole call: it asks for the whole split of small sizes, by a bound of up
+// to 4 MiB that grows with every size.
+size_t call_min_bytes(const Shape& s) {
+  if (!sa::mfma_bwd_supported(s)) return stage_min_bytes(s);
+  return std::max(stage_min_bytes(s), std::min(sa::mfma_bwd_max_bytes(s), size_t(4) << 20));
+}
+size_t call_bytes(const Shape& s) {
+  if (!sa::mfma_bwd_supported(s)) return sa::f32_bwd_plan(s).bytes;
+  return std::max(sa::mfma_bwd_plan(s).bytes, call_min_bytes(s));
+}
+
 size_t workspace_bytes_for(int64_t B, int64_t N, int64_t H, int64_t D, int32_t w1, int32_t w2,
                            int32_t dtype) {
   if (check_sizes(B, N, H, D, w1, w2, dtype) != SA_OK) return 0;
-  if (choose_path(1, B, N, H, D, w1, w2, dtype) == Path::Mfma)
-    return sa::mfma_bwd_plan(make_shape(B, N, H, D, w1, w2, 1.0f, dtype)).bytes;
-  const Shape s = make_shape(B, N, H, D, w1, w2, 1.0f, dtype);
-  return sa::f32_bwd_plan(s).bytes;
+  return call_bytes(make_shape(B, N, H, D, w1, w2, 1.0f, dtype));
 }
 
 // Backward workspace of the determinant logits: the MFMA plan where the MFMA kernels take the shape, else Delta only.
@@ -90,7 +106,7 @@ size_t det_workspace_bytes_for(int64_t B, int64_t N, int64_t H, int64_t D, int32
   if (check_sizes(B, N, H, D, w1, w2, dtype) != SA_OK) return 0;
   Shape s = make_shape(B, N, H, D, w1, w2, 1.0f, dtype);
   s.form = 1;
-  if (sa::mfma_bwd_supported(s)) return sa::mfma_bwd_plan(s).bytes;
+  if (sa::mfma_bwd_supported(s)) return call_bytes(s);
   return ((static_cast<size_t>(B * H * N) * sizeof(float)) + 255) & ~size_t(255);
 }
 
@@ -123,7 +139,7 @@ GqaLayout gqa_layout(int64_t B, int64_t N, int64_t H, int64_t Hkv, int64_t D, in
   s.Hkv = static_cast<int>(Hkv);
   // (the grouped plan may split its fewer key blocks further)
   l.base = workspace_bytes_for(B, N, H, D, w1, w2, dtype);
-  if (native) l.base = std::max(l.base, sa::mfma_bwd_plan(s).bytes);
+  if (native) l.base = std::max(l.base, call_bytes(s));
   l.base = (l.base + 255) & ~size_t(255);
   l.bytes = l.base + (native ? 2 : 8) * l.per_tensor;
   return l;
@@ -131,13 +147,14 @@ GqaLayout gqa_layout(int64_t B, int64_t N, int64_t H, int64_t Hkv, int64_t D, in
 
 int to_status(hipError_t e) { return e == hipSuccess ? SA_OK : SA_ERR_HIP; }
 
-// Common validation of the backward entry points (pointers checked by callers).
+// Common validation of the backward entry points (pointers checked by callers);
+// `need`: stage_min_bytes or call_min_bytes.
 int check_bwd(int64_t B, int64_t N, int64_t H, int64_t D, int32_t w1, int32_t w2, float scale,
-              int32_t dtype, size_t workspace_bytes) {
+              int32_t dtype, size_t workspace_bytes, size_t need(const Shape&)) {
   if (!isfinite(scale)) return SA_ERR_INVALID;
   const int rc = check_sizes(B, N, H, D, w1, w2, dtype);
   if (rc != SA_OK) return rc;
-  if (workspace_bytes < workspace_bytes_for(B, N, H, D, w1, w2, dtype)) return SA_ERR_WORKSPACE;
+  if (workspace_bytes < need(make_shape(B, N, H, D, w1, w2, scale, dtype))) return SA_ERR_WORKSPACE;
   return SA_OK;
 }
 
@@ -178,11 +195,12 @@ int run_stage(const Shape& s, Path path, BwdStage stage, const void* q, const vo
     return to_status(
         sa::mfma_bwd_stage(s, stage, q, k, kp, v, vp, dout, lse, g0, g1, g2, workspace, st));
   // Trilinear logits take the float32 MFMA kernels; determinant logits, the
-  // query side of w2 > 128 (whose k-rows overflow the LDS ring) and strides past
-  // 32-bit offsets the plain ones.
+  // query side of w2 > 128 (whose k-rows overflow the LDS ring) or of a small
+  // workspace and strides past 32-bit offsets the plain ones.
   const float* delta = static_cast<const float*>(workspace);
-  if (stage == BwdStage::Key ? sa::f32_bwd_key_supported(s) : sa::f32_bwd_query_supported(s)) {
-    float* halo = reinterpret_cast<float*>(static_cast<char*>(workspace) + sa::f32_bwd_plan(s).halo_off);
+  const sa::F32Plan plan = sa::f32_bwd_plan(s);
+  if (stage == BwdStage::Key ? sa::f32_bwd_key_supported(s) : sa::f32_bwd_query_supported(s) && !plan.plain) {
+    float* halo = reinterpret_cast<float*>(static_cast<char*>(workspace) + plan.halo_off);
     return to_status(sa::f32_bwd_stage(s, stage, q, k, kp, v, vp, dout, lse, delta, g0, g1, g2, halo, st));
   }
   return to_status(sa::generic_bwd_stage(s, stage, q, k, kp, v, vp, dout, lse, delta, g0, g1, g2, st));
@@ -275,7 +293,7 @@ int simplicial_attn_bwd_preprocess(const void* out, const void* dout, void* work
                                    size_t workspace_bytes, int64_t B, int64_t N, int64_t H,
                                    int64_t D, int32_t w1, int32_t w2, int32_t dtype, void* stream) {
   if (check_ptrs({out, dout, workspace}) != SA_OK) return SA_ERR_INVALID;
-  const int rc = check_bwd(B, N, H, D, w1, w2, 1.0f, dtype, workspace_bytes);
+  const int rc = check_bwd(B, N, H, D, w1, w2, 1.0f, dtype, workspace_bytes, stage_min_bytes);
   if (rc != SA_OK) return rc;
   const Shape s = make_shape(B, N, H, D, w1, w2, 1.0f, dtype);
   return run_delta(s, choose_path(1, B, N, H, D, w1, w2, dtype), out, dout, workspace,
@@ -289,9 +307,10 @@ int simplicial_attn_bwd_query_side(const void* q, const void* k, const void* kp,
                                    int32_t w2, float scale, int32_t dtype, void* stream) {
   if (check_ptrs({q, k, kp, v, vp, dout, lse, dq, dkp, dvp, workspace}) != SA_OK)
     return SA_ERR_INVALID;
-  const int rc = check_bwd(B, N, H, D, w1, w2, scale, dtype, workspace_bytes);
+  const int rc = check_bwd(B, N, H, D, w1, w2, scale, dtype, workspace_bytes, stage_min_bytes);
   if (rc != SA_OK) return rc;
-  const Shape s = make_shape(B, N, H, D, w1, w2, scale, dtype);
+  Shape s = make_shape(B, N, H, D, w1, w2, scale, dtype);
+  s.ws_cap = workspace_bytes;
   return run_stage(s, choose_path(1, B, N, H, D, w1, w2, dtype), BwdStage::Query, q, k, kp, v, vp,
                    dout, lse, dq, dkp, dvp, workspace, static_cast<hipStream_t>(stream));
 }
@@ -302,9 +321,10 @@ int simplicial_attn_bwd_key_side(const void* q, const void* k, const void* kp, c
                                  int64_t N, int64_t H, int64_t D, int32_t w1, int32_t w2,
                                  float scale, int32_t dtype, void* stream) {
   if (check_ptrs({q, k, kp, v, vp, dout, lse, dk, dv, workspace}) != SA_OK) return SA_ERR_INVALID;
-  const int rc = check_bwd(B, N, H, D, w1, w2, scale, dtype, workspace_bytes);
+  const int rc = check_bwd(B, N, H, D, w1, w2, scale, dtype, workspace_bytes, stage_min_bytes);
   if (rc != SA_OK) return rc;
-  const Shape s = make_shape(B, N, H, D, w1, w2, scale, dtype);
+  Shape s = make_shape(B, N, H, D, w1, w2, scale, dtype);
+  s.ws_cap = workspace_bytes;
   return run_stage(s, choose_path(1, B, N, H, D, w1, w2, dtype), BwdStage::Key, q, k, kp, v, vp,
                    dout, lse, dk, dv, nullptr, workspace, static_cast<hipStream_t>(stream));
 }
@@ -336,9 +356,10 @@ int simplicial_attn_bwd_biased(const void* q, const void* k, const void* kp, con
   if (check_ptrs({q, k, kp, v, vp, out, dout, lse, dq, dk, dkp, dv, dvp, workspace}) != SA_OK)
     return SA_ERR_INVALID;
   if (!isfinite(kp_bias) || !isfinite(vp_bias)) return SA_ERR_INVALID;
-  const int rc = check_bwd(B, N, H, D, w1, w2, scale, dtype, workspace_bytes);
+  const int rc = check_bwd(B, N, H, D, w1, w2, scale, dtype, workspace_bytes, call_min_bytes);
   if (rc != SA_OK) return rc;
   Shape s = make_shape(B, N, H, D, w1, w2, scale, dtype);
+  s.ws_cap = workspace_bytes;
   s.kp_bias = kp_bias;
   s.vp_bias = vp_bias;
   const Path path = choose_path(1, B, N, H, D, w1, w2, dtype);
@@ -355,8 +376,8 @@ size_t simplicial_attn_bwd_fused_workspace_size(int64_t B, int64_t N, int64_t H,
                                                 int32_t w2, int32_t dtype) {
   if (check_sizes(B, N, H, D, w1, w2, dtype) != SA_OK) return 0;
   const Shape s = make_shape(B, N, H, D, w1, w2, 1.0f, dtype);
-  // The preprocess stage asks for the split backward's workspace.
-  return fused_path(s) ? std::max(sa::mfma_fused_plan(s).bytes, sa::mfma_bwd_plan(s).bytes) : 0;
+  // (never less than the split backward's, so that one workspace serves both)
+  return fused_path(s) ? std::max(sa::mfma_fused_plan(s).bytes, call_bytes(s)) : 0;
 }
 
 // Validation shared by the fused entry points.
@@ -365,9 +386,9 @@ static int check_fused(int64_t B, int64_t N, int64_t H, int64_t D, int32_t w1, i
   if (!isfinite(scale)) return SA_ERR_INVALID;
   const int rc = check_sizes(B, N, H, D, w1, w2, dtype);
   if (rc != SA_OK) return rc;
-  const size_t need = simplicial_attn_bwd_fused_workspace_size(B, N, H, D, w1, w2, dtype);
-  if (need == 0) return SA_ERR_UNSUPPORTED;
-  return workspace_bytes < need ? SA_ERR_WORKSPACE : SA_OK;
+  const Shape s = make_shape(B, N, H, D, w1, w2, scale, dtype);
+  if (!fused_path(s)) return SA_ERR_UNSUPPORTED;
+  return workspace_bytes < sa::mfma_fused_plan(s).bytes ? SA_ERR_WORKSPACE : SA_OK;
 }
 
 int simplicial_attn_bwd_fused(const void* q, const void* k, const void* kp, const void* v,
@@ -452,9 +473,10 @@ int simplicial_attn_det_bwd(const void* q, const void* k, const void* kp, const 
   if (!isfinite(scale)) return SA_ERR_INVALID;
   const int rc = check_sizes(B, N, H, D, w1, w2, dtype);
   if (rc != SA_OK) return rc;
-  if (workspace_bytes < det_workspace_bytes_for(B, N, H, D, w1, w2, dtype)) return SA_ERR_WORKSPACE;
   Shape s = make_shape(B, N, H, D, w1, w2, scale, dtype);
   s.form = 1;
+  if (workspace_bytes < call_min_bytes(s)) return SA_ERR_WORKSPACE;
+  s.ws_cap = workspace_bytes;
   const Path path = sa::mfma_bwd_supported(s) ? Path::Mfma : Path::Generic;
   hipStream_t st = static_cast<hipStream_t>(stream);
   int r = run_delta(s, path, out, dout, workspace, st);
@@ -479,15 +501,21 @@ int simplicial_attn_bwd_gqa(const void* q, const void* k, const void* kp, const 
   if (check_ptrs({q, k, kp, v, vp, out, dout, lse, dq, dk, dkp, dv, dvp, workspace}) != SA_OK)
     return SA_ERR_INVALID;
   if (Hkv <= 0 || Hkv > H || H % Hkv != 0) return SA_ERR_INVALID;
-  const int rc = check_bwd(B, N, H, D, w1, w2, scale, dtype, SIZE_MAX);
+  const int rc = check_bwd(B, N, H, D, w1, w2, scale, dtype, workspace_bytes, call_min_bytes);
   if (rc != SA_OK) return rc;
-  const GqaLayout l = gqa_layout(B, N, H, Hkv, D, w1, w2, dtype);
-  if (workspace_bytes < l.bytes) return SA_ERR_WORKSPACE;
   if (Hkv == H)
     return simplicial_attn_bwd(q, k, kp, v, vp, out, dout, lse, dq, dk, dkp, dv, dvp, workspace,
                                workspace_bytes, B, N, H, D, w1, w2, scale, dtype, stream);
+  GqaLayout l = gqa_layout(B, N, H, Hkv, D, w1, w2, dtype);
   Shape s = make_shape(B, N, H, D, w1, w2, scale, dtype);
+  const size_t tensors = (gqa_native(s) ? 2 : 8) * l.per_tensor;
+  size_t need = call_min_bytes(s);
   s.Hkv = static_cast<int>(Hkv);
+  need = (std::max(need, call_min_bytes(s)) + 255) & ~size_t(255);
+  if (workspace_bytes < need + tensors) return SA_ERR_WORKSPACE;
+  // What is left beside the tensors is the per-head backward's workspace.
+  l.base = std::min(l.base, (workspace_bytes - tensors) & ~size_t(255));
+  s.ws_cap = l.base;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
   if (gqa_native(s)) {

@@ -49,16 +49,15 @@ BwdPlan mfma_bwd_plan(const Shape& s) {
   for (long c = cq / 2; c >= p.W2P && bh * ((s.N + 127) / 128) <= 2048; c /= 2)
     if (cost(c) < 0.95 * cost(cq)) cq = c;
   while (cq < 1024 && bh * ((s.N + cq - 1) / cq) > 4096) cq *= 2;
-  const size_t halo_rows = static_cast<size_t>(p.W2P - 1);
   const size_t delta_bytes = ((bh * static_cast<size_t>(s.N) * 4) + 255) & ~size_t(255);
   auto set_chunk = [&](long c) {
     p.CQ = static_cast<int>(c);
     p.nchunks = static_cast<int>((s.N + c - 1) / c);
-    p.halo_floats = bh * static_cast<size_t>(p.nchunks) * halo_rows * s.D;
+    p.halo_floats = bh * static_cast<size_t>(p.nchunks) * (p.W2P - 1) * s.D;
     p.bytes = delta_bytes + 4 * p.halo_floats * 4;
   };
   set_chunk(cq);
-  // A capped workspace takes longer chunks (one chunk per head at most).
+  // A smaller workspace takes longer chunks (one chunk per head at most).
   while (s.ws_cap > 0 && p.bytes > s.ws_cap && cq < s.N) {
     cq *= 2;
     set_chunk(cq);
@@ -82,6 +81,20 @@ BwdPlan mfma_bwd_plan(const Shape& s) {
     if ((s.ws_cap == 0 || p.key_off + ks * key_bytes <= s.ws_cap) && key_cost(ks) < 0.95 * key_cost(p.ks)) p.ks = ks;
   if (p.ks > 1) p.bytes = p.key_off + p.ks * key_bytes;
   return p;
+}
+
+size_t mfma_bwd_min_bytes(const Shape& s) {
+  const size_t bh = static_cast<size_t>(s.B) * s.H;
+  size_t cq = 128;
+  while (cq < 1024 && bh * ((s.N + cq - 1) / cq) > 4096) cq *= 2;
+  const size_t halo_floats = bh * ((s.N + cq - 1) / cq) * (s.w2 <= 32 ? 31 : 63) * s.D;
+  return ((bh * s.N * 4 + 255) & ~size_t(255)) + 16 * halo_floats;
+}
+
+size_t mfma_bwd_max_bytes(const Shape& s) {
+  const size_t bh = static_cast<size_t>(s.B) * s.H, w2p = s.w2 <= 32 ? 32 : 64;
+  const size_t halo_floats = bh * ((s.N + w2p - 1) / w2p) * (w2p - 1) * s.D;
+  return ((bh * s.N * 4 + 255) & ~size_t(255)) + 16 * halo_floats + 64 * static_cast<size_t>(s.B) * s.N * s.Hkv * s.D;
 }
 
 namespace {

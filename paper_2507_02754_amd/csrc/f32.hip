@@ -1399,6 +1399,15 @@ F32Plan f32_bwd_plan(const Shape& s) {
     while (cq > 16 && bh * ((s.N + cq - 1) / cq) < 512) cq /= 2;
     set_chunk(cq);
     while (p.CQ < s.N && (bh * p.nchunks > 4096 || !fits(p.key_floats))) set_chunk(2l * p.CQ);
+    // Chunks of more than an eighth of all queries, in a workspace of little
+    // more than Delta: a workgroup's walk then takes longer than one thread per
+    // pair on the whole chip. One chunk per head of N=2000 D=64 w1=256 w2=16,
+    // float32: 14.5 ms for 1 to 32 heads, the plain kernels 2.2, 4.3, 8.4, 16.6
+    // (8 heads), 33.1 ms; N=1024 D=128 w1=w2=128, bf16: 35 ms and 5.8 .. 44 (8), 88.
+    if (p.CQ > 128 && 8l * p.CQ > bh * s.N) {
+      p.plain = true;
+      set_chunk(s.N);
+    }
   }
   // Key side: a key block's row blocks go to up to four workgroups while there
   // are too few key blocks for the CUs (the sum costs a launch: 5 us).

@@ -25,9 +25,9 @@ struct Shape {
   // Logit form: 0 trilinear (Section 4), 1 sum of 3 x 3 determinants over
   // 3-component chunks (Section 5).
   int form;
-  // Largest backward workspace the caller can provide, in bytes (0: no
-  // limit). The MFMA backward plan lengthens its query chunks until its
-  // workspace fits (fewer chunk-boundary partial sums).
+  // Bytes of the caller's backward workspace (0: no limit). The plans split the
+  // work no further than its partial sums fit: longer query chunks (fewer
+  // chunk-boundary sums), fewer workgroups per key block.
   size_t ws_cap;
   // Constants added to every element of K' and V' after loading (the
   // K2_BIAS / V2_BIAS constants of the paper's Appendix B kernel); 0 for the
@@ -70,10 +70,11 @@ hipError_t f32_fwd(const Shape& s, const void* q, const void* k, const void* kp,
 // halo_off the query side's partial dk' / dv' rows (halo_floats per array: head /
 // tail x dk' / dv' as in BwdPlan, or, `full`, dk' and dv' of every k-row a chunk
 // touches; none with one chunk per head) and, key_floats further, the key side's
-// partial sums ([ks, 2, B*H, N, D], ks > 1 only).
+// partial sums ([ks, 2, B*H, N, D], ks > 1 only). `plain`: the workspace leaves
+// too few chunks, the query side runs faster on the plain kernels.
 struct F32Plan {
   int lw, groups, W2T, qs, CQ, nchunks, ks;
-  bool full;
+  bool full, plain;
   size_t halo_floats, key_floats, halo_off, bytes;
 };
 F32Plan f32_bwd_plan(const Shape& s);
@@ -96,6 +97,10 @@ struct BwdPlan {
   size_t halo_floats, delta_off, halo_off, key_off, bytes;
 };
 BwdPlan mfma_bwd_plan(const Shape& s);
+// Bytes of its smallest workspace: chunks of 128 queries or more, ks = 1.
+size_t mfma_bwd_min_bytes(const Shape& s);
+// Bytes no plan of the shape passes: the shortest chunks, ks = 8.
+size_t mfma_bwd_max_bytes(const Shape& s);
 bool mfma_bwd_supported(const Shape& s);
 hipError_t mfma_bwd_delta(const Shape& s, const void* out, const void* dout, void* workspace,
                           hipStream_t st);
