@@ -34,7 +34,11 @@ BIASED = [
     (1, 1, 129, 128, 33, 7, "bf16", -1.0, 0.5),     # rows outside the w2 window stay excluded
     (2, 1, 200, 64, 40, 32, "bf16", 0.5, 0.5),      # head_dim 64
     (1, 1, 333, 128, 96, 64, "bf16", 0.3, -0.7),    # w2 = 64 (two wavefronts per query)
-    (1, 2, 100, 64, 7, 5, "fp32", 1.5, -0.25),      # plain kernels
+    (1, 2, 100, 64, 7, 5, "fp32", 1.5, -0.25),      # float32 MFMA kernels
+    (1, 2, 101, 64, 33, 40, "fp32", 0.5, -1.0),     # two row groups
+    (1, 2, 150, 32, 40, 16, "bf16", 0.75, -0.5),    # bf16 data there: do~ and q~ in three parts
+    (1, 1, 160, 128, 48, 96, "bf16", -0.5, 0.75),
+    (1, 1, 150, 16, 40, 130, "bf16", 0.5, 0.5),     # its query side on the plain kernels
 ]
 
 

@@ -128,7 +128,9 @@ GQA = [
     (1, 4, 2, 300, 128, 64, 32, "bf16"),   # MFMA path, two query heads per K-side head
     (2, 8, 1, 200, 64, 40, 32, "bf16"),    # head_dim 64, all query heads on one K-side head (head-folded)
     (1, 4, 2, 333, 128, 96, 64, "bf16"),   # w2 = 64 (two wavefronts per query)
-    (1, 6, 3, 100, 64, 7, 5, "fp32"),      # generic path
+    (1, 6, 3, 100, 64, 7, 5, "fp32"),      # float32 MFMA kernels
+    (1, 4, 2, 120, 128, 50, 70, "bf16"),   # bf16 data there, three row groups
+    (1, 4, 1, 90, 32, 33, 16, "bf16"),
     (1, 3, 3, 129, 128, 33, 7, "bf16"),    # Hkv == H
     (1, 64, 1, 96, 64, 40, 32, "bf16"),    # 64 query heads per K-side head (Section 6's ratio)
     (1, 8, 2, 257, 128, 100, 17, "bf16"),  # head-folded, w1 and w2 not multiples of 32

@@ -27,7 +27,7 @@ def test_noalloc_rejects_sizes_beyond_the_scratch_before_any_hip_call():
     rc = lib.simplicial_attn_bwd_noalloc(*([fake] * 13), B, N, H, D, 512, 32, 0.088, 1, None)
     assert rc == SA_ERR_SCRATCH
     assert "scratch" in lib.simplicial_attn_error_string(rc).decode()
-    # generic path (fp32): same limit
+    # float32 data: same limit
     rc = lib.simplicial_attn_bwd_noalloc(*([fake] * 13), B, N, H, 64, 16, 8, 0.125, 0, None)
     assert rc == SA_ERR_SCRATCH
     # arguments are still validated first
@@ -49,7 +49,7 @@ def test_noalloc_matches_workspace_backward():
     """Calls in a row on one GPU, larger first: the benchmark shape (its
     workspace exceeds the array, so the query side walks longer chunks), then
     sizes whose workspace fits (bitwise equal to simplicial_attn_bwd), the
-    w2 = 64 path and the plain fp32 path. Each call is checked against the
+    w2 = 64 path and the float32 path. Each call is checked against the
     workspace backward on the same inputs at the parity bar."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU visible")
