@@ -48,6 +48,8 @@
 #include "f32_offsets.h"
 #include "mfma_common.h"
 
+#include <algorithm>
+
 namespace sa {
 namespace {
 
@@ -946,7 +948,7 @@ __global__ __launch_bounds__(kFThreads, D == 128 ? 1 : 2) void bwd_query_f32_ker
 // dk', dv' of the k-rows that left the query side as partial sums, added in the
 // order of the chunks. Chunks of at least W2T queries: the W2T - 1 rows before
 // each boundary, tail of chunk c - 1 plus head of chunk c. plan.full: every row,
-// over the chunks whose queries see it.
+// over the chunks whose queries see it (up to W2T of them: eight loads in flight).
 template <typename T>
 __global__ __launch_bounds__(256) void fixup_f32_kernel(Shape s, F32Plan plan, const float* __restrict__ ws,
                                                         T* __restrict__ dkp, T* __restrict__ dvp) {
@@ -962,6 +964,7 @@ __global__ __launch_bounds__(256) void fixup_f32_kernel(Shape s, F32Plan plan, c
     kr = static_cast<int>(row % s.N);
     const size_t per = static_cast<size_t>(plan.CQ + W1) * s.D;
     a = y = 0.f;
+#pragma unroll 8
     for (int c = kr / plan.CQ; c <= min(plan.nchunks - 1, (kr + W1) / plan.CQ); ++c) {
       const float* p = ws + (static_cast<size_t>(bh) * plan.nchunks + c) * per +
                        static_cast<size_t>(kr - (c * plan.CQ - W1)) * s.D + d;
@@ -1391,12 +1394,16 @@ F32Plan f32_bwd_plan(const Shape& s) {
       p.halo_floats = bh * static_cast<size_t>(p.nchunks) * rows * s.D;
       p.key_floats = (p.full ? 2 : 4) * p.halo_floats;
     };
-    // A workgroup per CU at least: from 128 queries down to 16 (one to four
-    // steps), below W2T at the price of a partial sum for every k-row. Longer
+    // A workgroup per CU at least: from 128 queries down to 16, below W2T at the
+    // price of a partial sum for every k-row; to a single step while the
+    // workgroups still fit the CUs at once (a chunk's steps run one after another:
+    // 24 us each at D=128 w2=128 and one key block; N=300 H=1 w1=1 w2=100 D=128:
+    // 381 us in chunks of 16, 76 in chunks of 2, 105 on the plain kernels). Longer
     // chunks where there are many (fewer boundary rows), and where the caller's
     // workspace is capped.
     long cq = 128;
     while (cq > 16 && bh * ((s.N + cq - 1) / cq) < 512) cq /= 2;
+    while (cq > p.qs * (32 >> p.lw) && bh * ((s.N + cq / 2 - 1) / (cq / 2)) <= 256) cq /= 2;
     set_chunk(cq);
     while (p.CQ < s.N && (bh * p.nchunks > 4096 || !fits(p.key_floats))) set_chunk(2l * p.CQ);
     // Chunks of more than an eighth of all queries, in a workspace of little
@@ -1410,10 +1417,16 @@ F32Plan f32_bwd_plan(const Shape& s) {
     }
   }
   // Key side: a key block's row blocks go to up to four workgroups while there
-  // are too few key blocks for the CUs (the sum costs a launch: 5 us).
+  // are too few key blocks for the CUs (the sum costs a launch: 5 us), to up to 16
+  // where that leaves every wavefront a row block and the workgroups fit the CUs
+  // at once (N=300 H=1 w1=1 w2=100 D=64: 56 us in four, 27 in 16, 25 on the plain
+  // kernels).
   const size_t n = bh * static_cast<size_t>(s.N) * s.D;
-  while (f32_bwd_key_supported(s) && p.ks < 4 && bh * ((s.N + 31) / 32) * p.ks < 192 &&
-         fits(p.key_floats + 4 * p.ks * n))
+  const long blocks = bh * ((s.N + 31) / 32);
+  const int SP = 32 >> p.lw, kw = s.D == 128 ? key_waves<128>() : key_waves<64>();
+  const long nrb = (std::min<long>(s.N, 31l + s.w1) + SP - 1) / SP * p.groups;  // row blocks of a key block
+  while (f32_bwd_key_supported(s) && fits(p.key_floats + 4 * p.ks * n) &&
+         (p.ks < 4 ? blocks * p.ks < 192 : p.ks < 16 && blocks * p.ks <= 128 && 2 * p.ks * kw <= nrb))
     p.ks *= 2;
   p.bytes += 4 * (p.key_floats + (p.ks > 1 ? 2 * p.ks * n : 0));
   return p;

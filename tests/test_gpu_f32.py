@@ -40,6 +40,9 @@ SHAPES = [
     (1, 1, 33, 16, 32, 32, "bf16"),
     (1, 1, 150, 64, 24, 130, "bf16"),    # query side on the plain kernels
     (1, 2, 210, 128, 40, 300, "bf16"),
+    (1, 1, 300, 16, 1, 100, "fp32"),     # chunks of one query or two, 16 workgroups per key block
+    (1, 1, 140, 128, 2, 128, "bf16"),
+    (1, 2, 90, 64, 9, 12, "fp32"),       # chunks of one step of eight queries
 ]
 
 
