@@ -1398,9 +1398,13 @@ F32Plan f32_bwd_plan(const Shape& s) {
     // price of a partial sum for every k-row; to a single step while the
     // workgroups still fit the CUs at once (a chunk's steps run one after another:
     // 24 us each at D=128 w2=128 and one key block; N=300 H=1 w1=1 w2=100 D=128:
-    // 381 us in chunks of 16, 76 in chunks of 2, 105 on the plain kernels). Longer
-    // chunks where there are many (fewer boundary rows), and where the caller's
-    // workspace is capped.
+    // 381 us in chunks of 16, 76 in chunks of 2, 105 on the plain kernels). 512:
+    // up to two workgroups share a CU; stopping at 256 costs 14 to 30% (N=3000 H=4
+    // D=64 w1=256 w2=32 float32 704 us for 619, N=3000 H=8 D=128 w1=100 w2=8 568
+    // for 434), going on to 1024 gains nothing (617, 444). Longer chunks where
+    // there are more than 4096 (within 1% of a limit of 1024 or 16384 at 8000 to
+    // 33000 chunks: it bounds the partial sums), and where the caller's workspace
+    // is capped.
     long cq = 128;
     while (cq > 16 && bh * ((s.N + cq - 1) / cq) < 512) cq /= 2;
     while (cq > p.qs * (32 >> p.lw) && bh * ((s.N + cq / 2 - 1) / (cq / 2)) <= 256) cq /= 2;
@@ -1420,7 +1424,9 @@ F32Plan f32_bwd_plan(const Shape& s) {
   // are too few key blocks for the CUs (the sum costs a launch: 5 us), to up to 16
   // where that leaves every wavefront a row block and the workgroups fit the CUs
   // at once (N=300 H=1 w1=1 w2=100 D=64: 56 us in four, 27 in 16, 25 on the plain
-  // kernels).
+  // kernels). 192 key blocks: a limit of 128 leaves N=1024 H=4 D=128 w1=w2=128
+  // whole (1310 us for 684; 119 -> 103 us at N=600 H=4 D=64 w1=256 w2=16), one of
+  // 256 splits where the CUs are nearly full (N=2000 H=4 D=64: 204 us for 193).
   const size_t n = bh * static_cast<size_t>(s.N) * s.D;
   const long blocks = bh * ((s.N + 31) / 32);
   const int SP = 32 >> p.lw, kw = s.D == 128 ? key_waves<128>() : key_waves<64>();

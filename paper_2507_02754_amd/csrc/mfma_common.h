@@ -230,7 +230,10 @@ __device__ __forceinline__ u32x4_t frag_tr_swz(const char* tile, int lane, int d
 //     plus immediates (2048 dt + 256 u), each half-wavefront covering all 64
 //     banks once;
 //   * staging stores of 4 (D = 128) or 8 (D = 64) full rows per wavefront
-//     instruction that touch every bank equally (the minimum LDS cycles).
+//     instruction; the 16 consecutive lanes that store a row's chunks (two
+//     rows' at D = 64) fall on four 16-byte bank slots (eight), so that the
+//     instruction takes 16 passes (8) where 4 would do (counted among the query
+//     side's bank conflicts).
 template <int D>
 struct FragTile {
   static constexpr int CH = D / 8;  // 16-byte chunks per row
