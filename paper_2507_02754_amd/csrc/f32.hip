@@ -18,12 +18,12 @@
 //     add their float32 sums in a fixed order.
 //
 // Measured, forward + backward: float32, B=1 H=4 N=2000 D=64 w1=256 w2=16, 16.8 ms
-// on the plain kernels (one thread per pair, operands read per pair), 0.50 ms
-// here; bf16, N=1024 D=128 w1=w2=128, 44.8 ms and 2.55 ms (1.55 ms on
-// bf16 parts, below). The matrix cores are
-// busy 60% of the time at these sizes. Vector instructions are what costs the
-// rest: they add to the products' time even with two wavefronts per SIMD (6.9
-// per product: 0.54 ms; masks and operand checks on the edge blocks only: 0.50 ms), while loads issued further ahead of their use
+// on the plain kernels (one thread per pair, operands read per pair), 0.51 ms
+// here; bf16, N=1024 D=128 w1=w2=128, 44.8 ms and 2.55 ms (1.55 ms on bf16 parts,
+// below). The matrix cores are busy 60% of the time at these sizes. Vector
+// instructions are what costs the rest: they add to the products' time even with
+// two wavefronts per SIMD (6.9 per product: 0.54 ms; masks and operand checks on
+// the edge blocks only: 0.51 ms), while loads issued further ahead of their use
 // changed nothing.
 //
 // Operand layout (lane = 32 h + c). A row operand (rows along the lanes): lane

@@ -31,8 +31,8 @@ class SimplicialAttention(nn.Module):
     """2-simplicial attention layer (Section 4) over sliding windows (w1, w2).
 
     x [B, N, d_model] -> [B, N, d_model]. Attention runs in `attn_dtype`
-    (bf16: the MFMA kernels for head_dim 64/128 and w2 <= 64; fp32: the plain
-    kernels); the projections run in the dtype of the module's parameters.
+    (bf16: the bf16 MFMA kernels for head_dim 64/128 and w2 <= 64; fp32 and the
+    other bf16 shapes: the float32 MFMA kernels); the projections run in the dtype of the module's parameters.
     """
 
     def __init__(self, d_model, n_heads, head_dim, w1, w2, kv_heads=None, kp_bias=0.0, vp_bias=0.0,
