@@ -63,11 +63,14 @@ constexpr float kLn2Lo = static_cast<float>(0.69314718055994530942 - static_cast
 // 2^(x - lse log2 e) with lse log2 e as hi + lo: the normaliser's product is not
 // rounded before the difference (it is several times larger than the differences
 // that matter). x has the scale in its q~, rounded as in the forward: its errors
-// then largely cancel against those in lse.
+// then largely cancel against those in lse. An infinite lse has no low part (its
+// remainder is NaN): +inf gives probabilities of 0, a query left out.
 struct Norm {
   float hi, lo;
-  __device__ __forceinline__ explicit Norm(float lse)
-      : hi(lse * kLog2e), lo(__builtin_fmaf(lse, kLog2eLo, __builtin_fmaf(lse, kLog2e, -hi))) {}
+  __device__ __forceinline__ explicit Norm(float lse) : hi(lse * kLog2e) {
+    const float r = __builtin_fmaf(lse, kLog2eLo, __builtin_fmaf(lse, kLog2e, -hi));
+    lo = fabsf(hi) < __builtin_inff() ? r : 0.f;
+  }
 };
 __device__ __forceinline__ float prob(float x, const Norm& n) { return fast_exp2((x - n.hi) - n.lo); }
 

@@ -232,3 +232,23 @@ def test_f32_delta_of_2_to_the_30_rows():
     assert delta[rows].tolist() == [4.0 * x for x in range(1, 6)]
     delta[rows] = 2.0
     assert float(delta.min()) == 2.0 and float(delta.max()) == 2.0
+
+
+@pytest.mark.parametrize("n,d,w1,w2,dt", [(150, 64, 40, 16, "fp32"), (90, 128, 30, 40, "bf16"), (100, 32, 50, 5, "bf16"),
+                                          (80, 16, 20, 130, "fp32")])
+def test_f32_infinite_lse_leaves_a_query_out(n, d, w1, w2, dt):
+    """An LSE of +inf makes a query's probabilities 0, as a huge one does: it adds
+    nothing to any gradient, and its own dq is 0."""
+    dtype = torch.float32 if dt == "fp32" else torch.bfloat16
+    print(f"\n[f32] infinite LSE N={n} D={d} w2={w2} {dt}", flush=True)
+    x = [t.cuda() for t in draw((1, n, 2, d), seed=n + w2, dtype=dtype)]
+    o, lse = simplicial_attn_fwd(*x[:5], w1, w2)
+    runs = []
+    for big in (1e30, float("inf")):
+        l2 = lse.clone()
+        l2[:, 1, ::7] = big
+        runs.append(simplicial_attn_bwd(*x[:5], o, x[5], l2, w1, w2))
+    torch.cuda.synchronize()
+    for name, a, b in zip(P.GRAD_NAMES, *runs):
+        assert torch.isfinite(a).all() and torch.equal(a, b), name
+    assert bool((runs[1][0][:, ::7, 1] == 0).all())
