@@ -9,7 +9,8 @@ import torch
 
 import parity as P
 from paper_2507_02754_amd import binding, load_library
-from paper_2507_02754_amd import (simplicial_attn_bwd, simplicial_attn_bwd_gqa,
+from paper_2507_02754_amd import (simplicial_attn_bwd, simplicial_attn_bwd_fused, simplicial_attn_bwd_fused_reduce,
+                                  simplicial_attn_bwd_gqa,
                                   simplicial_attn_bwd_gqa_workspace_size, simplicial_attn_bwd_key_side,
                                   simplicial_attn_bwd_noalloc, simplicial_attn_bwd_preprocess,
                                   simplicial_attn_bwd_query_side, simplicial_attn_bwd_workspace_size,
@@ -155,3 +156,26 @@ def test_noalloc_with_a_smaller_split(n, h, d, w1, w2, dtype, changed):
         assert torch.equal(a, r) == (name not in changed), name
         a, r = a.double(), r.double()
         assert bool(((a - r).abs() <= _order_bound(r, dtype)).all()), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,h,w1,w2", [(100, 2, 7, 5), (64, 1, 16, 32), (700, 4, 100, 17)])
+def test_fused_stages_with_the_fused_plans_bytes(n, h, w1, w2):
+    """Delta and the fused kernel's partial sums are enough for its three calls, also
+    where the two-kernel backward's whole split takes more."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    print(f"\n[workspace] fused N={n} H={h} w1={w1} w2={w2}", flush=True)
+    d, scale = 128, 128 ** -0.5
+    need = (4 * n * h + 255) // 256 * 256 + 4 * h * -(-n // 64) * ((63 + w1) + 2 * (94 + w1)) * d
+    x = [t.cuda() for t in draw((1, n, h, d), seed=n)]
+    o, lse = simplicial_attn_fwd(*x[:5], w1, w2, scale)
+    buf = torch.full((need + 65536,), 0x5A, dtype=torch.uint8, device="cuda")
+    ws = buf[:need]
+    simplicial_attn_bwd_preprocess(o, x[5], w1, w2, ws)
+    dk, dv = simplicial_attn_bwd_fused(*x, lse, w1, w2, ws, scale)
+    dq, dkp, dvp = simplicial_attn_bwd_fused_reduce(x[0], w1, w2, ws, scale)
+    ref = simplicial_attn_bwd(*x[:5], o, x[5], lse, w1, w2, scale)
+    torch.cuda.synchronize()
+    assert bool((buf[need:] == 0x5A).all())
+    P.check_grads([P.to64(g) for g in (dq, dk, dkp, dv, dvp)], [P.to64(g) for g in ref], "bf16", "fused")
